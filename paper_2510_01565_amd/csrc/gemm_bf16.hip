@@ -20,6 +20,7 @@
 
 #include "device_common.h"
 
+
 namespace dit {
 
 namespace {
@@ -238,6 +239,7 @@ __global__ __launch_bounds__(NWM* NWN * 64) void gemm_bf16_kernel(const GemmProb
     constexpr int FM2 = 2 * FM, FN2 = FN16;             // 16-row / 16-column fragments per wave tile
     constexpr int NR2 = FM2 + FN2;                      // fragment reads per k-step
     constexpr int NMP = FM * FN2;                       // MFMAs per phase
+    constexpr bool PINGPONG = BM == 256 && BN == 256;
     static_assert(B_REGION + STAGES * B_STAGE <= (int)sizeof(lds), "LDS");
     static_assert((STAGES - 1) * A_STAGE + (FM2 - 1) * 16 * ROWB < 65536 &&
                   (STAGES - 1) * B_STAGE + (FN2 - 1) * 16 * ROWB < 65536, "ds_read immediate offsets");
@@ -299,7 +301,162 @@ __global__ __launch_bounds__(NWM* NWN * 64) void gemm_bf16_kernel(const GemmProb
             16, vo, koff, 0, 0);
       }
     };
-    if constexpr (FM2 + FN2 <= FM * FN2) {
+    if constexpr (PINGPONG) {
+      // The 256x256 tile.  Two wave groups (waves 0-3 and 4-7, one wave of each
+      // per SIMD) take turns: while one issues a cluster of 16 MFMAs, the other
+      // reads the fragments of its next cluster and issues its share of the
+      // loads, so LDS reads, loads and MFMAs run beside each other all the time
+      // instead of every wave reading at once; block barriers hold the groups
+      // one turn apart.  A K tile is Q clusters.  Cluster c multiplies the
+      // wave's c-th quarter of A rows (2 fragments) with all its B columns;
+      // A and B tiles lie in LDS as Q parts, part c holding every wave's c-th
+      // quarter side by side.  Read phase k = Q kt + c takes part c of A of
+      // tile kt and part c of B of tile kt + 1 (B fragments are held for a
+      // whole tile, two tiles in turn), 6 reads in every phase.  A part is
+      // read in one phase, and the loads of the part two tiles on leave into
+      // its place in the next phase: the other group read it one turn earlier,
+      // ahead of the barrier in between.  A load has 2Q - 2 read phases (1.5 K
+      // tiles) until the wait before the barrier that makes it visible.
+      // Every output is summed in the same order as in the other schedules.
+      // Rate at 16384 x 3072 x 15360 (plain store): 1.44 - 1.50 PFLOP/s against
+      // 1.35 - 1.42 with the schedule below, matrix cores busy 0.89 of the
+      // cycles against 0.77 at a clock that power holds at 1.63 against 1.77
+      // GHz; 4608 x 9216 x 3072: 1.29 against 1.23.  Tiles of fewer MFMAs per
+      // phase (256x128, 128x256) gain 4 - 10% on repeated launches but lose
+      // 1 - 3% inside a step, where operands and code arrive cold, and keep the
+      // schedule below; raised priority for the MFMA turn and a barrier ahead
+      // of its last MFMAs measured 1% and 18% slower.
+      constexpr int Q = 4;
+      constexpr int AF = FM2 / Q, BF = FN2, BQ = FN2 / Q;  // A fragments of a cluster; B fragments in all, and per phase
+      constexpr int ASUB = A_STAGE / Q, BSUB = B_STAGE / Q;  // bytes of a part
+      constexpr int LA = AI / Q, LB = BI / Q;                // load instructions of a part per wave
+      static_assert(NWAVES == 8 && AF * Q == FM2 && BQ * Q == FN2 && LA * Q == AI && LB * Q == BI, "ping-pong tile");
+      const int lds0 = (int)(unsigned)(size_t)(__attribute__((address_space(3))) char*)lbase;
+      // per-lane LDS addresses of fragment 0 of part 0, stage 0, for the two k-steps
+      int ar[2], br[2];
+      {
+        const int ra = wm * (WTM / Q) + (lane & 15), rb = wn * (WTN / Q) + (lane & 15);
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+          ar[ks] = lds0 + lds_slot<CPR>(ra, 4 * ks + (lane >> 4)) * 16;
+          br[ks] = lds0 + B_REGION + lds_slot<CPR>(rb, 4 * ks + (lane >> 4)) * 16;
+        }
+      }
+      // per-lane global byte offsets of this wave's load instructions of each part
+      int pa[Q][LA], pb[Q][LB];
+#pragma unroll
+      for (int c = 0; c < Q; ++c) {
+        const int sl = lane % CPR;
+#pragma unroll
+        for (int q = 0; q < LA; ++q) {
+          const int row = (wv * LA + q) * RPI + lane / CPR;
+          const int kc = lds_slot<CPR>(row, sl) - row * CPR;
+          pa[c][q] = ((m0 + row / (WTM / Q) * WTM + c * (WTM / Q) + row % (WTM / Q)) * (int)lda + kc * 8) * 2;
+        }
+#pragma unroll
+        for (int q = 0; q < LB; ++q) {
+          const int row = (wv * LB + q) * RPI + lane / CPR;
+          const int kc = lds_slot<CPR>(row, sl) - row * CPR;
+          pb[c][q] = ((n0 + row / (WTN / Q) * WTN + c * (WTN / Q) + row % (WTN / Q)) * (int)ldw + kc * 8) * 2;
+        }
+      }
+      // part c of K tile kt into stage st
+      auto load_a = [&](auto stc, auto cc, int kt) __attribute__((always_inline)) {
+        constexpr int st = decltype(stc)::value, c = decltype(cc)::value;
+        const int koff = (kb + min(kt, KT - 1)) * BK * 2;
+#pragma unroll
+        for (int q = 0; q < LA; ++q) {
+          const int vo = pa[c][q];
+          __builtin_amdgcn_raw_ptr_buffer_load_lds(
+              rsa,
+              (__attribute__((address_space(3))) void*)(lbase + st * A_STAGE + c * ASUB + (wv * LA + q) * RPI * ROWB),
+              16, vo, koff, 0, 0);
+        }
+      };
+      auto load_b = [&](auto stc, auto cc, int kt) __attribute__((always_inline)) {
+        constexpr int st = decltype(stc)::value, c = decltype(cc)::value;
+        const int koff = (kb + min(kt, KT - 1)) * BK * 2;
+#pragma unroll
+        for (int q = 0; q < LB; ++q) {
+          const int vo = pb[c][q];
+          __builtin_amdgcn_raw_ptr_buffer_load_lds(
+              rsw,
+              (__attribute__((address_space(3))) void*)(lbase + B_REGION + st * B_STAGE + c * BSUB +
+                                                        (wv * LB + q) * RPI * ROWB),
+              16, vo, koff, 0, 0);
+        }
+      };
+      i32x4_t fa[2][AF], fb[2][2][BF];  // A fragments [k-step][row], B fragments [tile parity][k-step][column]
+      auto read_a = [&](auto stc, auto cc) __attribute__((always_inline)) {
+        constexpr int off = decltype(stc)::value * A_STAGE + decltype(cc)::value * ASUB;
+        static_for<2 * AF>([&](auto ic) {
+          constexpr int ks = decltype(ic)::value / AF, i = decltype(ic)::value % AF;
+          asm_lds_read16<off + i * 16 * ROWB>(fa[ks][i], ar[ks]);
+        });
+      };
+      auto read_b = [&](auto stc, auto cc) __attribute__((always_inline)) {
+        constexpr int st = decltype(stc)::value, c = decltype(cc)::value, off = st * B_STAGE + c * BSUB;
+        static_for<2 * BQ>([&](auto ic) {
+          constexpr int ks = decltype(ic)::value / BQ, j = decltype(ic)::value % BQ;
+          asm_lds_read16<off + j * 16 * ROWB>(fb[st][ks][c * BQ + j], br[ks]);
+        });
+      };
+      // one read phase and the cluster it feeds
+      auto phase = [&](auto stc, auto cc, int kt) __attribute__((always_inline)) {
+        constexpr int st = decltype(stc)::value, c = decltype(cc)::value;
+        using SN = std::integral_constant<int, st ^ 1>;
+        using CP = std::integral_constant<int, (c + Q - 1) % Q>;
+        using SA = std::integral_constant<int, c == 0 ? st ^ 1 : st>;
+        using SB = std::integral_constant<int, c == 0 ? st : st ^ 1>;
+        read_a(stc, cc);
+        read_b(SN{}, cc);
+        load_a(SA{}, CP{}, c == 0 ? kt + 1 : kt + 2);
+        load_b(SB{}, CP{}, c == 0 ? kt + 2 : kt + 3);
+        asm_lgkm_wait<0>();
+        wait_vmcnt<(2 * Q - 2) * (LA + LB)>();
+        asm volatile("s_barrier" ::: "memory");
+        static_for<2 * AF * BF>([&](auto mc) {
+          constexpr int m = decltype(mc)::value, ks = m / (AF * BF), i = m % (AF * BF) / BF, j = m % BF;
+          asm_mfma16(acc16[c * AF + i][j], fa[ks][i], fb[st][ks][j]);
+        });
+        asm volatile("s_barrier" ::: "memory");
+      };
+#pragma unroll
+      for (int i = 0; i < AM; ++i)
+#pragma unroll
+        for (int j = 0; j < AN; ++j) asm volatile("" : "+v"(acc16[i][j]));
+      using S0 = std::integral_constant<int, 0>;
+      using S1 = std::integral_constant<int, 1>;
+      static_for<Q>([&](auto cc) { load_b(S0{}, cc, 0); });
+      static_for<Q>([&](auto cc) {
+        load_a(S0{}, cc, 0);
+        load_b(S1{}, cc, 1);
+      });
+      wait_vmcnt<Q * (LA + LB)>();
+      asm volatile("s_barrier" ::: "memory");
+      static_for<Q>([&](auto cc) { read_b(S0{}, cc); });
+      asm_lgkm_wait<0>();
+      asm volatile("s_barrier" ::: "memory");
+      static_for<Q - 1>([&](auto cc) {
+        load_a(S1{}, cc, 1);
+        load_b(S0{}, cc, 2);
+      });
+      wait_vmcnt<(2 * Q - 2) * (LA + LB)>();
+      asm volatile("s_barrier" ::: "memory");
+      if (wv >= 4) asm volatile("s_barrier" ::: "memory");
+      int kt = 0;
+      for (; kt + 1 < KT; kt += 2) {
+        static_for<Q>([&](auto cc) { phase(S0{}, cc, kt); });
+        static_for<Q>([&](auto cc) { phase(S1{}, cc, kt + 1); });
+      }
+      if (kt < KT) static_for<Q>([&](auto cc) { phase(S0{}, cc, kt); });
+      if (wv < 4) asm volatile("s_barrier" ::: "memory");
+      asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7" ::: "memory");
+#pragma unroll
+      for (int i = 0; i < AM; ++i)
+#pragma unroll
+        for (int j = 0; j < AN; ++j) asm volatile("" : "+v"(acc16[i][j]));
+    } else if constexpr (FM2 + FN2 <= FM * FN2) {
       // Every configuration whose phase holds at least one MFMA per fragment
       // read (all but the 128x64 skinny tile): the schedule below with every
       // MFMA, fragment read, LDS wait and barrier an asm statement, so the
@@ -790,7 +947,7 @@ hipError_t launch_cfg(const GemmProblem& p, int sk, hipStream_t s) {
 template <int BM, int BN, int NWM, int NWN, int BK, int STAGES>
 hipError_t launch_cfg_dtl_only(const GemmProblem& p, int sk, hipStream_t s) {
   if (dtl_ok<BM, BN, BK>(p)) return launch_kernel<BM, BN, NWM, NWN, BK, STAGES, true>(p, sk, s);
-  return launch_cfg<256, 256, 4, 2, 64, 2>(p, 1, s);
+  return launch_cfg<256, 256, 2, 4, 64, 2>(p, 1, s);
 }
 
 enum GemmCfg { CFG_128x64 = 0, CFG_256x256 = 1, CFG_128x128 = 2, CFG_256x128 = 3, CFG_128x256 = 4, CFG_288x192 = 5 };
@@ -955,7 +1112,7 @@ hipError_t launch_gemm_bf16(const GemmProblem& p, hipStream_t s) {
     case CFG_128x64:
       return launch_cfg<128, 64, 4, 1, 64, 2>(p, 1, s);
     case CFG_256x256:
-      return launch_cfg<256, 256, 4, 2, 64, 2>(p, c.sk, s);
+      return launch_cfg<256, 256, 2, 4, 64, 2>(p, c.sk, s);
     case CFG_256x128:
       return launch_cfg<256, 128, 4, 2, 64, 2>(p, c.sk, s);
     case CFG_128x256:
