@@ -94,6 +94,140 @@ __device__ __forceinline__ void asm_lgkm_wait() {
   if constexpr (N < 15) asm volatile("s_waitcnt lgkmcnt(%0)" ::"i"(N));
 }
 
+// One staged group of 32 rows x W columns of a tile, corner (m, n), bias added
+// (staging pitch W + 4 floats).  Consecutive lanes take consecutive 16-byte
+// pieces of an output row, so a wave's access covers whole runs of W columns;
+// a lane's loads all leave before its first store (one in-order counter holds
+// both).  H and the head dimension are multiples of 64 and n and W of 16, so
+// an 8-column piece lies in one head of one of Q, K, V or the MLP input, but a
+// group of 48 columns need not.
+template <int W>
+__device__ __forceinline__ void epilogue_group(const EpiArgs& E, const RowEntry* rows, const float* stg, int m, int n,
+                                               int M, int N, int lane) {
+  constexpr int SP = W + 4;
+  if (n >= N || m >= M) return;
+  const int v0 = E.mode == EPI_QKV ? 2 * E.hidden : N, v1 = E.mode == EPI_QKV ? 3 * E.hidden : N;  // V columns
+  if (n < v1 && n + W > v0) {
+    // a lane takes one column and 16 consecutive rows, which (when they are 16
+    // consecutive, 16-aligned padded positions of one request) land in one
+    // aligned 16-key group of V^T: two 16-byte stores
+    const int hn = n + lane - v0, h = hn / E.head_dim, dd = hn - h * E.head_dim;
+    if (lane < W && n + lane >= v0 && n + lane < v1 && n + lane < N) {
+      bf16_t* vt = (bf16_t*)E.vt + ((long)h * E.head_dim + dd) * E.vt_ld;
+#pragma unroll
+      for (int r16 = 0; r16 < 32; r16 += 16) {
+        if (m + r16 >= M) break;
+        const RowEntry r0 = rows[r16];
+        if (m + r16 + 15 < M && (r0.pos & 15) == 0 && rows[r16 + 15].pos == r0.pos + 15) {
+          // slot s of the group holds key vt_slot(s): swap the middle quads
+          float w[16];
+#pragma unroll
+          for (int q = 0; q < 16; ++q) w[q] = stg[(r16 + vt_slot(q)) * SP + lane];
+          store16<bf16_t>(vt + r0.pos, w);
+        } else {
+          for (int q = 0; q < 16; ++q)
+            if (m + r16 + q < M) vt[vt_slot(rows[r16 + q].pos)] = f2bf(stg[(r16 + q) * SP + lane]);
+        }
+      }
+    }
+    if (n >= v0 && n + W <= v1) return;
+  }
+  if (E.mode == EPI_RESID || E.mode == EPI_STORE_F32) {
+    constexpr int PPR = W / 4, NP = 16 * PPR / 64;  // 16-byte pieces of a row, pieces of a lane in half the rows
+    float* const o = (float*)E.out + (long)m * E.ldo + n;
+    const int last = M - 1 - m, cols = N - n;
+#pragma unroll 1
+    for (int l0 = lane; l0 < 128 * NP; l0 += 64 * NP) {
+      float4 v[NP];
+      if (E.mode == EPI_RESID) {  // N is a multiple of 4; pieces past the edges load the last row or piece
+        const float* const gate = E.mods + E.gate_off + n;
+#pragma unroll
+        for (int t = 0; t < NP; ++t) {
+          const int id = l0 + 64 * t, r = min(id / PPR, last), c = min(id % PPR * 4, cols - 4);
+          v[t] = *(const float4*)(o + (long)r * E.ldo + c);
+        }
+#pragma unroll
+        for (int t = 0; t < NP; ++t) {
+          const int id = l0 + 64 * t, r = min(id / PPR, last), c = min(id % PPR * 4, cols - 4);
+          const float4 g = *(const float4*)(gate + (long)rows[r].req * E.mods_ld + c);
+          const float4 y = *(const float4*)&stg[r * SP + c];
+          v[t].x += g.x * y.x;
+          v[t].y += g.y * y.y;
+          v[t].z += g.z * y.z;
+          v[t].w += g.w * y.w;
+        }
+      } else {
+#pragma unroll
+        for (int t = 0; t < NP; ++t) {
+          const int id = l0 + 64 * t;
+          v[t] = *(const float4*)&stg[id / PPR * SP + id % PPR * 4];
+        }
+      }
+#pragma unroll
+      for (int t = 0; t < NP; ++t) {
+        const int id = l0 + 64 * t, r = id / PPR, c = id % PPR * 4;
+        float* const dst = o + (long)r * E.ldo + c;
+        if (r > last) continue;
+        if (c + 4 <= cols) {
+          *(float4*)dst = v[t];
+        } else {
+          if (c < cols) dst[0] = v[t].x;
+          if (c + 1 < cols) dst[1] = v[t].y;
+          if (c + 2 < cols) dst[2] = v[t].z;
+        }
+      }
+    }
+    return;
+  }
+  constexpr int PPR = W / 8, NP = 32 * PPR / 64;
+#pragma unroll 1
+  for (int t = 0; t < NP; ++t) {
+    const int id = lane + 64 * t, r = id / PPR, c = id % PPR * 8, nc = n + c;
+    float v[8];
+    *(float4*)&v[0] = *(const float4*)&stg[r * SP + c];
+    *(float4*)&v[4] = *(const float4*)&stg[r * SP + c + 4];
+    bf16_t* dst;
+    if (E.mode == EPI_QKV && nc < v0) {
+      const int d = E.head_dim, k = nc >= E.hidden, hn = nc - k * E.hidden, h = hn / d, dd = hn - h * d;
+      const RowEntry re = rows[r];  // garbage past row M, not used then
+      if (m + r < M && re.gi >= 0) {
+        const int half = d >> 1;
+        const int pos = dd < half ? re.gi : re.gj;
+        const float4* cs = (const float4*)(E.rope + pos * (d >> 2) + ((dd < half ? dd : dd - half) >> 1));
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          const float4 t4 = cs[q];
+          const float u0 = v[4 * q], w0 = v[4 * q + 1], u1 = v[4 * q + 2], w1 = v[4 * q + 3];
+          v[4 * q] = u0 * t4.x - w0 * t4.y;
+          v[4 * q + 1] = u0 * t4.y + w0 * t4.x;
+          v[4 * q + 2] = u1 * t4.z - w1 * t4.w;
+          v[4 * q + 3] = u1 * t4.w + w1 * t4.z;
+        }
+      }
+      dst = (bf16_t*)(k ? E.k : E.q) + ((long)h * E.T + re.pos) * d + dd;
+    } else {
+      if (E.mode != EPI_STORE_T)
+#pragma unroll
+        for (int q = 0; q < 8; ++q) v[q] = gelu_tanh(v[q]);
+      if (E.mode == EPI_QKV) dst = (bf16_t*)E.gelu_out + (long)(m + r) * E.gelu_ld + E.gelu_col0 + (nc - E.n_qkv);
+      else dst = (bf16_t*)E.out + (long)(m + r) * E.ldo + (E.mode == EPI_GELU ? E.col0 : 0) + nc;
+    }
+    if (m + r >= M || nc >= N || (nc >= v0 && nc < v1)) continue;
+    if (nc + 8 <= N) {
+      uint4 w;
+      w.x = pack_bf16x2(v[0], v[1]);
+      w.y = pack_bf16x2(v[2], v[3]);
+      w.z = pack_bf16x2(v[4], v[5]);
+      w.w = pack_bf16x2(v[6], v[7]);
+      *(uint4*)dst = w;
+    } else {
+#pragma unroll
+      for (int q = 0; q < 7; ++q)
+        if (nc + q < N) dst[q] = f2bf(v[q]);
+    }
+  }
+}
+
 template <int BM, int BN, int NWM, int NWN, int BK, int STAGES, bool DTL>
 __global__ __launch_bounds__(NWM* NWN * 64) void gemm_bf16_kernel(const GemmProblem P) {
   constexpr int NT = NWM * NWN * 64;
@@ -757,17 +891,16 @@ __global__ __launch_bounds__(NWM* NWN * 64) void gemm_bf16_kernel(const GemmProb
   }
 
   // epilogue.  Row facts (request, padded position, grid position) are computed
-  // once per tile row into LDS, so the unrolled loops never index the batch
-  // metadata.  Each 32x32 accumulator fragment is staged through a per-wave
-  // LDS buffer so that a lane ends up with 16 consecutive columns of one row
-  // and stores them with 16-byte writes.
+  // once per tile row into LDS, so the loop never indexes the batch metadata.
+  // The wave tile leaves in groups of 32 rows, each staged through a per-wave
+  // LDS buffer.
   RowEntry* rows = (RowEntry*)&lds[0];
-  constexpr int SP = 36;  // staging row pitch in floats (16-byte aligned rows)
+  constexpr int SP = WTN + 4;  // staging row pitch in floats (16-byte aligned rows)
   float* stg = (float*)&lds[0] + BM * (sizeof(RowEntry) / 4) + wave * 32 * SP;
-  static_assert(BM * sizeof(RowEntry) + NWAVES * 32 * SP * 4 <= sizeof(lds) - 16, "epilogue LDS (the last 16 bytes hold the split flag)");
+  static_assert(WTN <= 64 && BM * sizeof(RowEntry) + NWAVES * 32 * SP * 4 <= sizeof(lds) - 16,
+                "epilogue LDS (the last 16 bytes hold the split flag)");
   const EpiArgs E = gi ? P.g[1].epi : P.g[0].epi;
-  const bool need_rows = E.mode == EPI_RESID || E.mode == EPI_QKV;
-  if (need_rows) {
+  if (E.mode == EPI_RESID || E.mode == EPI_QKV) {
     for (int t = tid; t < BM; t += NT)
       if (m0 + t < M) rows[t] = make_row_entry(P.meta, E.row_base + m0 + t);
     __syncthreads();
@@ -775,8 +908,7 @@ __global__ __launch_bounds__(NWM* NWN * 64) void gemm_bf16_kernel(const GemmProb
   const bf16_t* bias = (const bf16_t*)E.bias;
   // The bias of every column this lane stages, loaded before the first output
   // store: loads and stores share one in-order counter, so a bias load issued
-  // after a column group's stores would wait for them, and the groups would
-  // follow one another at the latency of their stores.
+  // after a group's stores would wait for them.
   constexpr int NBC = DTL ? FN16 : FN;
   float bcol[NBC];
 #pragma unroll
@@ -784,124 +916,45 @@ __global__ __launch_bounds__(NWM* NWN * 64) void gemm_bf16_kernel(const GemmProb
     const int n = n0 + wn * WTN + (DTL ? q * 16 + (lane & 15) : q * 32 + (lane & 31));
     bcol[q] = (bias != nullptr && n < N) ? bf2f(bias[n]) : 0.f;
   }
-  const int rl = lane >> 1, cseg = (lane & 1) * 16;
-  // column groups of 32 (the last one 16 wide when the wave tile is an odd
-  // number of 16-column fragments)
-  constexpr int NJ = DTL ? (FN16 + 1) / 2 : FN;
-  // Row groups outer, column groups inner: a lane's consecutive column groups
-  // write adjacent pieces of the same rows (64 bytes of bf16 output each).
-  static_for<FM>([&](auto ii) {
-    constexpr int i = decltype(ii)::value;
-    static_for<NJ>([&](auto jj) {
-      constexpr int j = decltype(jj)::value;
-      constexpr int NB16 = DTL ? (FN16 - 2 * j < 2 ? FN16 - 2 * j : 2) : 2;  // 16-column blocks in the group
-      constexpr int NCOL = 16 * NB16;
-      const int nb = n0 + wn * WTN + j * 32;
-      const float bn = DTL ? 0.f : bcol[j];
-      // V^T columns of a QKV epilogue: a lane takes one column and 16 consecutive
-      // rows, which (when they are 16 consecutive, 16-aligned padded positions of
-      // one request) land in one aligned 16-key group of V^T: two 16-byte stores.
-      const bool vcols = E.mode == EPI_QKV && nb >= 2 * E.hidden && nb < 3 * E.hidden;
-      if constexpr (DTL) {
-        static_for<NB16>([&](auto bb) {
-          constexpr int b = decltype(bb)::value;
-          const float bn16 = bcol[2 * j + b];
-          static_for<2>([&](auto aa) {
-            constexpr int a = decltype(aa)::value;
-            static_for<4>([&](auto rr) {
-              constexpr int r = decltype(rr)::value;
-              stg[(a * 16 + 4 * (lane >> 4) + r) * SP + b * 16 + (lane & 15)] = acc16[2 * i + a][2 * j + b][r] + bn16;
+  // A rolled loop: only the staging writes, which name accumulator registers,
+  // have a copy per group.  Unrolled over its groups, modes and tails the
+  // epilogue was 240 KB of code for the 256x256 tile, run once per tile from
+  // an instruction cache (64 KB for two CUs) that the launches of a step,
+  // each another kernel, leave cold.  Rolled (the kernel is 25 KB), and with
+  // whole rows of the wave tile stored per wave access, the steps take 1 - 4%
+  // less: one single block at 256 px 239 -> 229 us, one double block at 512 px
+  // 520 -> 504 us, the 57-block 1024 px step 63.4 -> 62.4 ms, the SD3-shaped
+  // 512 px step 5.19 -> 4.97 ms.
+#pragma unroll 1
+  for (int g = 0; g < FM; ++g) {
+    static_for<FM>([&](auto gc) {
+      constexpr int i = decltype(gc)::value;
+      if (g == i) {
+        if constexpr (DTL) {
+          static_for<FN16>([&](auto jj) {
+            constexpr int j = decltype(jj)::value;
+            static_for<2>([&](auto aa) {
+              constexpr int a = decltype(aa)::value;
+              static_for<4>([&](auto rr) {
+                constexpr int r = decltype(rr)::value;
+                stg[(a * 16 + 4 * (lane >> 4) + r) * SP + j * 16 + (lane & 15)] = acc16[2 * i + a][j][r] + bcol[j];
+              });
             });
           });
-        });
-      } else {
-        static_for<16>([&](auto rr) {
-          constexpr int r = decltype(rr)::value;
-          stg[((r / 4) * 8 + (lane >> 5) * 4 + (r % 4)) * SP + (lane & 31)] = acc[i][j][r] + bn;
-        });
-      }
-      if (vcols) {
-        const int rh = lane >> 5, c = lane & 31;
-        float v[16];
-#pragma unroll
-        for (int q = 0; q < 16; ++q) v[q] = stg[(rh * 16 + q) * SP + c];
-        const int ml0 = wm * WTM + i * 32 + rh * 16;
-        const int m = m0 + ml0, n = nb + c;
-        if (c < NCOL && n < N && m < M) {
-          const RowEntry r0 = rows[ml0];
-          const bool whole = m + 15 < M && (r0.pos & 15) == 0 && rows[ml0 + 15].pos == r0.pos + 15;
-          const int hn = n - 2 * E.hidden, h = hn / E.head_dim, dd = hn - h * E.head_dim;
-          bf16_t* vt = (bf16_t*)E.vt + ((long)h * E.head_dim + dd) * E.vt_ld;
-          if (whole) {
-            // slot s of the group holds key vt_slot(s): swap the middle quads
-            float w[16];
-#pragma unroll
-            for (int q = 0; q < 16; ++q) w[q] = v[vt_slot(q)];
-            store16<bf16_t>(vt + r0.pos, w);
-          } else {
-#pragma unroll
-            for (int q = 0; q < 16; ++q)
-              if (m + q < M) vt[vt_slot(rows[ml0 + q].pos)] = f2bf(v[q]);
-          }
-        }
-        return;
-      }
-      if constexpr (NCOL == 16) {
-        if (E.mode == EPI_RESID) {
-          // a 16-wide group under the residual update: 8 columns per lane so
-          // that every lane of the wave reads, updates and writes x
-          const int c8 = (lane & 1) * 8;
-          const int ml = wm * WTM + i * 32 + rl;
-          const int m = m0 + ml, n = nb + c8;
-          if (m < M) {
-            const RowEntry re = rows[ml];
-            const float* g = E.mods + (long)re.req * E.mods_ld + E.gate_off + n;
-            float* xo = (float*)E.out + (long)m * E.ldo + n;
-            if (n + 8 <= N) {
-#pragma unroll
-              for (int q = 0; q < 2; ++q) {
-                const float4 t = *(const float4*)&stg[rl * SP + c8 + 4 * q];
-                const float4 gv = ((const float4*)g)[q];
-                float4 xv = ((float4*)xo)[q];
-                xv.x += gv.x * t.x;
-                xv.y += gv.y * t.y;
-                xv.z += gv.z * t.z;
-                xv.w += gv.w * t.w;
-                ((float4*)xo)[q] = xv;
-              }
-            } else {
-#pragma unroll
-              for (int q = 0; q < 8; ++q)
-                if (n + q < N) xo[q] += g[q] * stg[rl * SP + c8 + q];
-            }
-          }
-          return;
-        }
-      }
-      float v[16];
-      static_for<4>([&](auto qq) {
-        constexpr int q = decltype(qq)::value;
-        const float4 t = *(const float4*)&stg[rl * SP + cseg + 4 * q];
-        v[4 * q] = t.x;
-        v[4 * q + 1] = t.y;
-        v[4 * q + 2] = t.z;
-        v[4 * q + 3] = t.w;
-      });
-      const int ml = wm * WTM + i * 32 + rl;
-      const int m = m0 + ml, n = nb + cseg;
-      if (cseg < NCOL && m < M) {
-        RowEntry re;
-        if (need_rows) re = rows[ml];
-        if (n + 16 <= N) {
-          epilogue_segment16<bf16_t>(E, re, m, n, v);
         } else {
-#pragma unroll
-          for (int q = 0; q < 16; ++q)
-            if (n + q < N) epilogue_element<bf16_t>(E, re, m, n + q, v[q], v[q ^ 1]);
+          static_for<FN>([&](auto jj) {
+            constexpr int j = decltype(jj)::value;
+            static_for<16>([&](auto rr) {
+              constexpr int r = decltype(rr)::value;
+              stg[((r / 4) * 8 + (lane >> 5) * 4 + (r % 4)) * SP + j * 32 + (lane & 31)] = acc[i][j][r] + bcol[j];
+            });
+          });
         }
       }
     });
-  });
+    const int ml = wm * WTM + g * 32;
+    epilogue_group<WTN>(E, rows + ml, stg, m0 + ml, n0 + wn * WTN, M, N, lane);
+  }
 }
 
 // direct-to-LDS path: whole K tiles, 16-byte aligned rows, and operands

@@ -1,0 +1,52 @@
+"""Edges of the bf16 GEMM's main loop and epilogue on the GPU: the fewest K
+tiles of the 256x256 schedule, and output groups that end inside a wave tile
+or straddle the parts of a QKV row."""
+import numpy as np
+import pytest
+
+from paper_2510_01565_amd import dit, synth, workloads
+from harness import BF16_TOL, F32_TOL, host_params, normwise_err, request_inputs, to_dev
+from test_gpu_step import _oracle_step, _run_step
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("K", [64, 128, 320])   # 1, 2 and 5 K tiles
+@pytest.mark.parametrize("out", ["f32", "bf16"])
+def test_linear_256x256_few_k_tiles(K, out):
+    """Ragged rows and columns (2313 = 36 x 64 + 9); sampled outputs against fp64 dot products."""
+    import torch
+    M, N = 6001, 2313
+    x = synth.normal(11, "x", (M, K), bf16=True)
+    w = synth.normal(11, "w", (N, K), std=0.02, bf16=True)
+    b = synth.normal(11, "b", (N,), std=0.02, bf16=True)
+    y = torch.full((M, N), float("nan"), dtype=torch.float32 if out == "f32" else torch.bfloat16, device="cuda")
+    dit.profile_start()
+    dit.dit_linear(M, N, K, dit.DIT_BF16, to_dev(x, torch.bfloat16), to_dev(w, torch.bfloat16),
+                   to_dev(b, torch.bfloat16), y, dit.DIT_F32 if out == "f32" else dit.DIT_BF16)
+    torch.cuda.synchronize()
+    assert "gemm_bf16_256x256" in dit.profile_stop()
+    got = y.float().cpu().numpy()
+    assert np.isfinite(got).all()
+    rng = np.random.default_rng(K)
+    ms = np.concatenate([[0, M - 1, M - 1, M - 2], rng.integers(0, M, 2000)])
+    ns = np.concatenate([[0, N - 1, 0, N - 9], rng.integers(0, N, 2000)])
+    ref = (x[ms].astype(np.float64) * w[ns].astype(np.float64)).sum(axis=1) + b[ns].astype(np.float64)
+    # bf16 output: one rounding to 8 significant bits
+    assert normwise_err(got[ms, ns], ref) < (F32_TOL if out == "f32" else 2 ** -8)
+
+
+def test_step_width_not_a_multiple_of_the_wave_tile():
+    """Hidden size 640: 48-column wave tiles (288x192) straddle the Q / K and K / V boundaries of a
+    QKV row, and the rows of two packed requests of odd sizes end inside 16-row groups."""
+    m = workloads.ModelShape(hidden=640, heads=10, head_dim=64, mlp_ratio=4, n_double=1, n_single=1,
+                             in_channels=64, text_dim=96)
+    cfg, shapes, params = host_params(m, 12)
+    grids, n_txt, ts = [(40, 45), (3, 7)], [37, 5], [0.3, 0.8]
+    lat, txt = request_inputs(m, grids, n_txt, 12)
+    dit.profile_start()
+    vel, _, _ = _run_step(m, params, shapes, cfg, grids, n_txt, ts, lat, txt)
+    ran = dit.profile_stop()
+    assert "gemm_bf16_288x192" in ran, list(ran)
+    ref = np.concatenate(_oracle_step(m, params, grids, n_txt, ts, lat, txt))
+    assert normwise_err(vel.float().cpu().numpy(), ref) < BF16_TOL
