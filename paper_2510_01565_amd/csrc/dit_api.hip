@@ -396,12 +396,29 @@ hipError_t ln_mod(const Ctx& x, const float* X, int row_begin, int row_end, cons
   });
 }
 
-hipError_t gemv(hipStream_t s, int dtype, const void* W, const void* b, const float* xin, long ldx, int n_req, int K,
-                int N, int act, float* y, long ldy) {
-  const int es = dtype == DIT_BF16 ? 2 : 4;
-  const double bytes = (double)N * K * es + (double)N * es + 4.0 * n_req * ((double)K + N);
-  return timed(s, "gemv", 2.0 * n_req * (double)N * K, bytes,
-               [&] { return launch_gemv(dtype, W, b, xin, ldx, n_req, K, N, act, y, ldy, s); });
+hipError_t gemv(const Ctx& x, const void* W, const void* b, const float* xin, long ldx, int K, int N, int act,
+                const float* t, float* y, long ldy, const SetupArgs* setup) {
+  const int n = x.meta.n_req;
+  const double bytes = (double)N * K * x.es + (double)N * x.es + 4.0 * n * ((double)K + N);
+  return timed(x.s, "gemv", 2.0 * n * (double)N * K, bytes, [&] {
+    return launch_gemv(x.c->dtype, W, b, xin, ldx, n, K, N, act, t, y, ldy, setup, x.s);
+  });
+}
+
+// What the kernels of a call expect in its workspace; runs beside the call's first GEMV.
+SetupArgs setup_args(const Ctx& x) {
+  SetupArgs a{};
+  a.rope = x.ws.rope;
+  a.theta = (double)x.c->rope_theta;
+  a.zero = x.ws.sk_cnt;
+  a.n_zero = x.ws.sk_cnt ? kSplitMaxTiles : 0;
+  a.vt = x.ws.Vt;
+  a.vt_ld = x.ws.ldvt;
+  a.es = x.es;
+  a.heads = x.L.heads;
+  a.head_dim = x.L.d;
+  a.meta = x.meta;
+  return a;
 }
 
 EpiArgs epi_base(int mode, int row_base) {
@@ -699,16 +716,18 @@ dit_status run_step(const dit_config* cfg, const dit_weights* w, const dit_batch
   const int dt = cfg->dtype;
 
   // conditioning: c = W2 SiLU(W1 e(t) + b1) + b2; all modulation vectors m = Wm SiLU(c) + bm
-  HIP_TRY(timed(x.s, "setup", 0.0, 0.0, [&] { return launch_rope_table(x.ws.rope, x.L.d, cfg->rope_theta, x.s); }));
-  HIP_TRY(timed(x.s, "setup", 0.0, 0.0,
-                [&] { return launch_zero_i32(x.ws.sk_cnt, x.ws.sk_cnt ? kSplitMaxTiles : 0, x.s); }));
-  HIP_TRY(timed(x.s, "setup", 0.0, 0.0,
-                [&] { return launch_vt_pad_zero(dt, x.ws.Vt, x.ws.ldvt, meta, x.L.heads, x.L.d, x.s); }));
-  HIP_TRY(timed(x.s, "setup", 0.0, 0.0,
-                [&] { return launch_timestep_embed(x.ws.temb, n, batch->t, cfg->time_freq_dim, x.s); }));
-  HIP_TRY(gemv(x.s, dt, Wt(x, 0), Wt(x, 1), x.ws.temb, cfg->time_freq_dim, n, cfg->time_freq_dim, H, 0, x.ws.u, H));
-  HIP_TRY(gemv(x.s, dt, Wt(x, 2), Wt(x, 3), x.ws.u, H, n, H, H, 1, x.ws.cvec, H));
-  HIP_TRY(gemv(x.s, dt, Wt(x, 8), Wt(x, 9), x.ws.cvec, H, n, H, x.L.mod_rows, 1, x.ws.mods, x.L.mod_rows));
+  // (the embedding e(t) inside the first GEMV, up to 256 wide: a block evaluates it for itself)
+  const SetupArgs su = setup_args(x);
+  const int tf = cfg->time_freq_dim;
+  if (tf <= 256) {
+    HIP_TRY(gemv(x, Wt(x, 0), Wt(x, 1), nullptr, 0, tf, H, GEMV_TIMESTEP, batch->t, x.ws.u, H, &su));
+  } else {
+    HIP_TRY(timed(x.s, "setup", 0.0, 0.0, [&] { return launch_timestep_embed(x.ws.temb, n, batch->t, tf, x.s); }));
+    HIP_TRY(gemv(x, Wt(x, 0), Wt(x, 1), x.ws.temb, tf, tf, H, GEMV_PLAIN, nullptr, x.ws.u, H, &su));
+  }
+  HIP_TRY(gemv(x, Wt(x, 2), Wt(x, 3), x.ws.u, H, H, H, GEMV_SILU, nullptr, x.ws.cvec, H, nullptr));
+  HIP_TRY(gemv(x, Wt(x, 8), Wt(x, 9), x.ws.cvec, H, H, x.L.mod_rows, GEMV_SILU, nullptr, x.ws.mods, x.L.mod_rows,
+               nullptr));
 
   // input embedders -> residual stream X (stream-major rows)
   {
@@ -848,24 +867,20 @@ dit_status dit_block_forward(const dit_config* cfg, const dit_weights* w, int ki
   x.s = (hipStream_t)stream;
   x.es = elem_size(cfg->dtype);
   const int H = x.L.H, n = meta.n_req;
-  HIP_TRY(timed(x.s, "setup", 0.0, 0.0, [&] { return launch_rope_table(x.ws.rope, x.L.d, cfg->rope_theta, x.s); }));
-  HIP_TRY(timed(x.s, "setup", 0.0, 0.0,
-                [&] { return launch_zero_i32(x.ws.sk_cnt, x.ws.sk_cnt ? kSplitMaxTiles : 0, x.s); }));
-  HIP_TRY(timed(x.s, "setup", 0.0, 0.0,
-                [&] { return launch_vt_pad_zero(cfg->dtype, x.ws.Vt, x.ws.ldvt, meta, x.L.heads, x.L.d, x.s); }));
+  const SetupArgs su = setup_args(x);
   if (kind == 0) {
     // this block's modulation rows: image stream, then (untied) text stream
     const int off = x.L.mod_dbl(index, 0);
     const int rows = 6 * H * x.L.ns;
     const char* wm = (const char*)Wt(x, 8) + (long)off * H * x.es;
     const char* bm = (const char*)Wt(x, 9) + (long)off * x.es;
-    HIP_TRY(gemv(x.s, cfg->dtype, wm, bm, cond, H, n, H, rows, 1, x.ws.mods, rows));
+    HIP_TRY(gemv(x, wm, bm, cond, H, H, rows, GEMV_SILU, nullptr, x.ws.mods, rows, &su));
     return run_double(x, index, hidden, x.ws.mods, rows, 0, x.L.ns == 2 ? 6 * H : 0);
   }
   const int off = x.L.mod_sgl(index);
   const char* wm = (const char*)Wt(x, 8) + (long)off * H * x.es;
   const char* bm = (const char*)Wt(x, 9) + (long)off * x.es;
-  HIP_TRY(gemv(x.s, cfg->dtype, wm, bm, cond, H, n, H, 3 * H, 1, x.ws.mods, 3 * H));
+  HIP_TRY(gemv(x, wm, bm, cond, H, H, 3 * H, GEMV_SILU, nullptr, x.ws.mods, 3 * H, &su));
   return run_single(x, index, hidden, x.ws.mods, 3 * H, 0);
 }
 
@@ -918,7 +933,6 @@ dit_status dit_attention(const dit_batch* batch, int heads, int head_dim, int dt
   hipStream_t s = (hipStream_t)stream;
   HIP_TRY(timed(s, "v_transpose", 0.0, 2.0 * m.T * heads * head_dim * elem_size(dtype),
                 [&] { return launch_v_transpose(dtype, v, m, heads, head_dim, ws, s); }));
-  HIP_TRY(timed(s, "v_transpose", 0.0, 0.0, [&] { return launch_vt_pad_zero(dtype, ws, m.pad_off[m.n_req], m, heads, head_dim, s); }));
   AttnArgs a;
   memset(&a, 0, sizeof(a));
   const long Tp = m.pad_off[m.n_req];

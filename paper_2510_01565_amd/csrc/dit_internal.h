@@ -191,11 +191,27 @@ size_t attn_split_bytes(const BatchMeta& m, int heads, int head_dim);
 hipError_t launch_attention_f32(const AttnArgs& a, hipStream_t s);
 
 // elementwise / reduction kernels
-hipError_t launch_rope_table(float2* table, int head_dim, float theta, hipStream_t s);
+// What a call prepares in its workspace: the RoPE table, zeroed split counters
+// (n_zero ints) and zeroed V^T columns of the padding keys.
+struct SetupArgs {
+  float2* rope;  // [DIT_MAX_GRID][head_dim / 4]
+  double theta;
+  int* zero;
+  int n_zero;
+  void* vt;      // [heads * head_dim][vt_ld], elements of es bytes
+  long vt_ld;
+  int es, heads, head_dim;
+  BatchMeta meta;
+};
+constexpr int kSetupBlocks = 64;  // blocks of a launch that run it
+// e[r] = sinusoidal embedding of t_host[r], dim wide
 hipError_t launch_timestep_embed(float* e, int n_req, const float* t_host, int dim, hipStream_t s);
-// y[r, o] = sum_k W[o, k] * act(x[r, k]) + b[o]; act 0 = identity, 1 = SiLU
-hipError_t launch_gemv(int wdtype, const void* W, const void* b, const float* x, long ldx, int n_req,
-                       int K, int N, int act, float* y, long ldy, hipStream_t s);
+// y[r, o] = sum_k W[o, k] * a[r, k] + b[o], a = x, SiLU(x) or (GEMV_TIMESTEP,
+// x unused) the timestep embedding of t_host[r]; with `setup`, the launch also
+// runs the call's setup
+enum GemvAct : int { GEMV_PLAIN = 0, GEMV_SILU = 1, GEMV_TIMESTEP = 2 };
+hipError_t launch_gemv(int wdtype, const void* W, const void* b, const float* x, long ldx, int n_req, int K, int N,
+                       int act, const float* t_host, float* y, long ldy, const SetupArgs* setup, hipStream_t s);
 // adaLN LayerNorm of rows [row_begin, row_end) of X (fp32, ld H) into out (row 0 = row_begin)
 hipError_t launch_ln_modulate(int out_dtype, const float* X, int H, int row_begin, int row_end,
                               const BatchMeta& meta, const float* mods, int mods_ld, int shift_txt,
@@ -203,12 +219,9 @@ hipError_t launch_ln_modulate(int out_dtype, const float* X, int H, int row_begi
                               long ldo, hipStream_t s);
 hipError_t launch_euler(int dtype, void* x, const void* v, int channels, const BatchMeta& meta,
                         const float* dt_host, hipStream_t s);
-// v [T_joint, heads, d] (joint order) -> vt [heads][d][pad_off[n]] at columns vt_slot(padded position)
+// v [T_joint, heads, d] (joint order) -> vt [heads][d][pad_off[n]] at columns vt_slot(padded position),
+// the columns of padding keys zero; d a multiple of 64
 hipError_t launch_v_transpose(int dtype, const void* v, const BatchMeta& meta, int heads, int d, void* vt,
                               hipStream_t s);
-// n ints at p set to zero (a fill kernel, so a captured graph holds no memset node)
-hipError_t launch_zero_i32(int* p, int n, hipStream_t s);
-// zeroes the V^T columns of the padding keys of every request (padded positions >= the request length)
-hipError_t launch_vt_pad_zero(int dtype, void* vt, long ld, const BatchMeta& meta, int heads, int d, hipStream_t s);
 
 }  // namespace dit

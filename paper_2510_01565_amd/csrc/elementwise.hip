@@ -1,6 +1,7 @@
 // HBM-bound kernels of the step: adaLN LayerNorm, the modulation GEMV over
-// all blocks' adaLN weights, the timestep embedding, the RoPE angle table,
-// the Euler update and the V relayout of the stand-alone attention call.
+// all blocks' adaLN weights (whose launch also carries the timestep embedding
+// and a call's setup), the Euler update and the V relayout of the stand-alone
+// attention call.
 // Rows are processed one per wavefront with 16-byte accesses; all reductions
 // are fixed butterfly trees (bitwise deterministic).
 #include <math.h>
@@ -11,30 +12,48 @@ namespace dit {
 
 namespace {
 
-// ---------------------------------------------------------------- RoPE table
-// table[pos][k] = (cos, sin)(pos * theta^(-2k / (d/2))), evaluated in fp64.
-__global__ void rope_table_kernel(float2* table, int quarter, int axis_dim, double theta) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= DIT_MAX_GRID * quarter) return;
-  const int pos = i / quarter, k = i % quarter;
-  const double ang = (double)pos * pow(theta, -2.0 * k / axis_dim);
-  table[i] = make_float2((float)cos(ang), (float)sin(ang));
-}
-
 // ---------------------------------------------------------------- timestep embedding
 // e[r] = [cos(1000 t f_j) | sin(1000 t f_j)], f_j = 1e4^(-j/half), in fp64.
 struct TimeArgs {
   float t[kMaxReq];
 };
+__device__ __forceinline__ float timestep_value(float t, int k, int dim) {
+  const int half = dim / 2, j = k < half ? k : k - half;
+  const double ang = 1000.0 * (double)t * exp(-log(10000.0) * (double)j / half);
+  return (float)(k < half ? cos(ang) : sin(ang));
+}
 __global__ void timestep_kernel(float* e, int n_req, TimeArgs ta, int dim) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  const int half = dim / 2;
-  if (i >= n_req * half) return;
-  const int r = i / half, j = i % half;
-  const double f = exp(-log(10000.0) * (double)j / half);
-  const double ang = 1000.0 * (double)ta.t[r] * f;
-  e[(long)r * dim + j] = (float)cos(ang);
-  e[(long)r * dim + half + j] = (float)sin(ang);
+  if (i < n_req * dim) e[i] = timestep_value(ta.t[i / dim], i % dim, dim);
+}
+
+// ---------------------------------------------------------------- setup
+// What a call prepares in its workspace ahead of the first GEMM, spread over
+// `nblocks` blocks of 256 threads:
+//  the RoPE table, table[pos][k] = (cos, sin)(pos * theta^(-2k / (d/2))), in fp64;
+//  the split GEMMs' arrival counters, zeroed;
+//  the V^T columns of every request's padding keys, zeroed.
+__device__ __forceinline__ void setup_block(const SetupArgs& a, int block, int nblocks) {
+  const int t0 = block * 256 + threadIdx.x, stride = nblocks * 256;
+  const int quarter = a.head_dim / 4, axis = a.head_dim / 2;
+  for (int i = t0; i < DIT_MAX_GRID * quarter; i += stride) {
+    const int pos = i / quarter, k = i % quarter;
+    const double ang = (double)pos * pow(a.theta, -2.0 * k / axis);
+    a.rope[i] = make_float2((float)cos(ang), (float)sin(ang));
+  }
+  for (int i = t0; i < a.n_zero; i += stride) a.zero[i] = 0;
+  const int rows = a.heads * a.head_dim;
+  for (int r = 0; r < a.meta.n_req; ++r) {
+    const int L = a.meta.joint_off[r + 1] - a.meta.joint_off[r];
+    const int pad = a.meta.pad_off[r + 1] - a.meta.pad_off[r] - L;  // < 64
+    for (int i = t0; i < rows * 64; i += stride) {
+      const int k = i & 63;
+      if (k >= pad) continue;
+      const long at = (long)(i >> 6) * a.vt_ld + vt_slot(a.meta.pad_off[r] + L + k);
+      if (a.es == 2) ((uint16_t*)a.vt)[at] = 0;
+      else ((float*)a.vt)[at] = 0.f;
+    }
+  }
 }
 
 // ---------------------------------------------------------------- GEMV
@@ -47,6 +66,8 @@ __global__ void timestep_kernel(float* e, int n_req, TimeArgs ta, int dim) {
 // not displace cached data); on MI355X this streams the 6.5 GB of the FLUX
 // modulation weights at about 6.8 TB/s against 5.5 TB/s for one row per wave
 // with ordinary loads.
+// The first `sblocks` blocks run the call's setup (see setup_block), which
+// nothing in this launch reads.
 constexpr int GV_R = 4;
 constexpr int LN_MAX_H = 4096;  // widest hidden size (also the LayerNorm's limit)
 
@@ -60,20 +81,20 @@ struct GemvShape {
 template <typename WT, int MAXC>
 __global__ __launch_bounds__(256) void gemv_kernel(const WT* __restrict__ W, const WT* __restrict__ b,
                                                    const float* __restrict__ x, long ldx, int n_req, int K,
-                                                   int N, int act, float* __restrict__ y, long ldy) {
+                                                   int N, int act, float* __restrict__ y, long ldy, TimeArgs ta,
+                                                   int sblocks, const SetupArgs su) {
+  if ((int)blockIdx.x < sblocks) {
+    setup_block(su, blockIdx.x, sblocks);
+    return;
+  }
+  const int block = blockIdx.x - sblocks;
   using S = GemvShape<WT>;
   constexpr int EPC = S::EPC, V = S::V;
   typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
   extern __shared__ float xs[];  // [n_req][K]
   const int nr = min(n_req, GV_R);
-  for (int i = threadIdx.x; i < nr * K; i += blockDim.x) {
-    const int r = i / K, k = i % K;
-    float v = x[(long)r * ldx + k];
-    xs[i] = act ? silu(v) : v;
-  }
-  __syncthreads();
   const int lane = threadIdx.x & 63;
-  const int nwaves = gridDim.x * (blockDim.x >> 6);
+  const int nwaves = (gridDim.x - sblocks) * (blockDim.x >> 6);
   const int chunks = K / EPC;
   // Chunk i of a lane is chunk lane + 64 i of the row; lanes past the row's
   // last chunk load that chunk again (no branch around a load: a branch would
@@ -85,7 +106,17 @@ __global__ __launch_bounds__(256) void gemv_kernel(const WT* __restrict__ W, con
     cidx[i] = min(lane + 64 * i, chunks - 1);
     keep[i] = lane + 64 * i < chunks ? 1.f : 0.f;
   }
-  for (int o0 = (blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)) * V; o0 < N; o0 += nwaves * V) {
+  for (int i = threadIdx.x; i < nr * K; i += blockDim.x) {
+    const int r = i / K, k = i % K;
+    if (act == GEMV_TIMESTEP) {
+      xs[i] = timestep_value(ta.t[r], k, K);
+    } else {
+      const float v = x[(long)r * ldx + k];
+      xs[i] = act == GEMV_SILU ? silu(v) : v;
+    }
+  }
+  __syncthreads();
+  for (int o0 = (block * (blockDim.x >> 6) + (threadIdx.x >> 6)) * V; o0 < N; o0 += nwaves * V) {
     u32x4 u[V][MAXC];
 #pragma unroll
     for (int v = 0; v < V; ++v) {
@@ -227,113 +258,98 @@ __global__ void euler_kernel(T* __restrict__ x, const T* __restrict__ v, long n,
 }
 
 // ---------------------------------------------------------------- V relayout
+// v [T_joint][heads][d] -> V^T [heads][d][padded positions], columns in
+// vt_slot order, a request's padding keys zero.  A block moves 64 padded
+// positions x 64 dimensions of a head through LDS, with 16-byte loads along d
+// and 16-byte stores along the keys (a thread stores one 16-key group of one
+// row).  At 16 896 tokens and 6 heads of 128 (26 MB each way) 15 us with its
+// launch, against 43 us for element-wise accesses and a second launch for the
+// padding.
 template <typename T>
-__global__ void v_transpose_kernel(const T* __restrict__ v, const BatchMeta meta, int heads, int d,
-                                   T* __restrict__ vt, long ld) {
-  __shared__ T tile[32][33];
-  const int h = blockIdx.z;
-  const int p0 = blockIdx.x * 32, d0 = blockIdx.y * 32;
-  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;  // 32 x 8
-  const int T_ = meta.T;
-  for (int yy = ty; yy < 32; yy += 8) {
-    const int p = p0 + yy, dd = d0 + tx;
-    if (p < T_ && dd < d) tile[yy][tx] = v[((long)p * heads + h) * d + dd];
+__global__ __launch_bounds__(256) void v_transpose_kernel(const T* __restrict__ v, const BatchMeta meta, int heads,
+                                                          int d, T* __restrict__ vt, long ld) {
+  constexpr int E = 16 / sizeof(T);            // elements of a 16-byte piece
+  constexpr int WORDS = 64 * sizeof(T) / 4;    // 4-byte words of a tile row
+  constexpr int PITCH = WORDS + 1;             // odd: a column's rows fall on different banks
+  __shared__ uint32_t tile[64 * PITCH];
+  const int p0 = blockIdx.x * 64, d0 = blockIdx.y * 64, h = blockIdx.z;
+  int r = 0;  // pad_off are multiples of 64: the positions belong to one request
+  while (r + 1 < meta.n_req && p0 >= meta.pad_off[r + 1]) ++r;
+  const int q0 = p0 - meta.pad_off[r];
+  const int left = meta.joint_off[r + 1] - meta.joint_off[r] - q0;  // keys of the request from here on
+  const T* src = v + ((long)(meta.joint_off[r] + q0) * heads + h) * d + d0;
+#pragma unroll
+  for (int u = 0; u < 64 * 64 / E / 256; ++u) {
+    const int i = threadIdx.x + u * 256, row = i / (64 / E), c = i % (64 / E);
+    uint4 w = make_uint4(0, 0, 0, 0);
+    if (row < left) w = *(const uint4*)(src + (long)row * heads * d + c * E);
+    uint32_t* t = &tile[row * PITCH + c * 4];
+    t[0] = w.x;
+    t[1] = w.y;
+    t[2] = w.z;
+    t[3] = w.w;
   }
   __syncthreads();
-  for (int yy = ty; yy < 32; yy += 8) {
-    const int dd = d0 + yy, p = p0 + tx;
-    if (p < T_ && dd < d) {
-      int r = 0;
-      while (r + 1 < meta.n_req && p >= meta.joint_off[r + 1]) ++r;
-      const int col = vt_slot(meta.pad_off[r] + (p - meta.joint_off[r]));
-      vt[((long)h * d + dd) * ld + col] = tile[tx][yy];
-    }
-  }
-}
-
-template <typename T>
-__global__ void vt_pad_zero_kernel(T* __restrict__ vt, const BatchMeta meta, long ld) {
-  const long row = blockIdx.x;  // h * d + dd
-  for (int r = 0; r < meta.n_req; ++r) {
-    const int L = meta.joint_off[r + 1] - meta.joint_off[r];
-    const int P = meta.pad_off[r + 1] - meta.pad_off[r];
-    for (int k = L + threadIdx.x; k < P; k += blockDim.x) vt[row * ld + vt_slot(meta.pad_off[r] + k)] = T(0);
-  }
+  const int dd = threadIdx.x >> 2, g = (threadIdx.x & 3) * 16;
+  T o[16];
+#pragma unroll
+  for (int q = 0; q < 16; ++q) o[q] = ((const T*)&tile[(g + vt_slot(q)) * PITCH])[dd];
+  T* dst = vt + ((long)h * d + d0 + dd) * ld + p0 + g;
+#pragma unroll
+  for (int q = 0; q < 16 / E; ++q) *(uint4*)(dst + q * E) = *(const uint4*)(o + q * E);
 }
 
 }  // namespace
-
-namespace {
-__global__ void zero_i32_kernel(int* p, int n) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = 0;
-}
-}  // namespace
-
-hipError_t launch_zero_i32(int* p, int n, hipStream_t s) {
-  if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(zero_i32_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, p, n);
-  return hipGetLastError();
-}
-
-hipError_t launch_vt_pad_zero(int dtype, void* vt, long ld, const BatchMeta& meta, int heads, int d, hipStream_t s) {
-  const dim3 grid((unsigned)(heads * d));
-  if (dtype == DIT_BF16)
-    hipLaunchKernelGGL(vt_pad_zero_kernel<bf16_t>, grid, dim3(64), 0, s, (bf16_t*)vt, meta, ld);
-  else
-    hipLaunchKernelGGL(vt_pad_zero_kernel<float>, grid, dim3(64), 0, s, (float*)vt, meta, ld);
-  return hipGetLastError();
-}
-
-hipError_t launch_rope_table(float2* table, int head_dim, float theta, hipStream_t s) {
-  const int quarter = head_dim / 4;
-  const int n = DIT_MAX_GRID * quarter;
-  hipLaunchKernelGGL(rope_table_kernel, dim3((n + 255) / 256), dim3(256), 0, s, table, quarter, head_dim / 2,
-                     (double)theta);
-  return hipGetLastError();
-}
 
 hipError_t launch_timestep_embed(float* e, int n_req, const float* t_host, int dim, hipStream_t s) {
   TimeArgs ta{};
   for (int r = 0; r < n_req; ++r) ta.t[r] = t_host[r];
-  const int n = n_req * (dim / 2);
+  const int n = n_req * dim;
   hipLaunchKernelGGL(timestep_kernel, dim3((n + 255) / 256), dim3(256), 0, s, e, n_req, ta, dim);
   return hipGetLastError();
 }
 
 template <typename WT, int MAXC>
-void gemv_launch(int blocks, size_t shmem, hipStream_t s, const void* W, const void* b, const float* x, long ldx,
-                 int nr, int K, int N, int act, float* y, long ldy) {
-  hipLaunchKernelGGL((gemv_kernel<WT, MAXC>), dim3(blocks), dim3(256), shmem, s, (const WT*)W, (const WT*)b, x, ldx,
-                     nr, K, N, act, y, ldy);
+void gemv_launch(int blocks, int sblocks, size_t shmem, hipStream_t s, const void* W, const void* b, const float* x,
+                 long ldx, int nr, int K, int N, int act, float* y, long ldy, const TimeArgs& ta, const SetupArgs& su) {
+  hipLaunchKernelGGL((gemv_kernel<WT, MAXC>), dim3(blocks + sblocks), dim3(256), shmem, s, (const WT*)W, (const WT*)b,
+                     x, ldx, nr, K, N, act, y, ldy, ta, sblocks, su);
 }
 
-template <typename WT>
-void gemv_dispatch(int blocks, size_t shmem, hipStream_t s, const void* W, const void* b, const float* x, long ldx,
-                   int nr, int K, int N, int act, float* y, long ldy) {
+template <typename WT, class... A>
+void gemv_dispatch(int K, A&&... a) {
   const int c = (K / GemvShape<WT>::EPC + 63) / 64;  // chunks per lane and row
-  if (c <= 1) gemv_launch<WT, 1>(blocks, shmem, s, W, b, x, ldx, nr, K, N, act, y, ldy);
-  else if (c <= 2) gemv_launch<WT, 2>(blocks, shmem, s, W, b, x, ldx, nr, K, N, act, y, ldy);
-  else if (c <= 3) gemv_launch<WT, 3>(blocks, shmem, s, W, b, x, ldx, nr, K, N, act, y, ldy);
-  else if (c <= 4) gemv_launch<WT, 4>(blocks, shmem, s, W, b, x, ldx, nr, K, N, act, y, ldy);
-  else if (c <= 6) gemv_launch<WT, 6>(blocks, shmem, s, W, b, x, ldx, nr, K, N, act, y, ldy);
-  else if (c <= 8) gemv_launch<WT, 8>(blocks, shmem, s, W, b, x, ldx, nr, K, N, act, y, ldy);
-  else gemv_launch<WT, 16>(blocks, shmem, s, W, b, x, ldx, nr, K, N, act, y, ldy);
+  if (c <= 1) gemv_launch<WT, 1>(a...);
+  else if (c <= 2) gemv_launch<WT, 2>(a...);
+  else if (c <= 3) gemv_launch<WT, 3>(a...);
+  else if (c <= 4) gemv_launch<WT, 4>(a...);
+  else if (c <= 6) gemv_launch<WT, 6>(a...);
+  else if (c <= 8) gemv_launch<WT, 8>(a...);
+  else gemv_launch<WT, 16>(a...);
 }
 
 hipError_t launch_gemv(int wdtype, const void* W, const void* b, const float* x, long ldx, int n_req, int K,
-                       int N, int act, float* y, long ldy, hipStream_t s) {
+                       int N, int act, const float* t_host, float* y, long ldy, const SetupArgs* setup,
+                       hipStream_t s) {
   if (K > LN_MAX_H) return hipErrorInvalidValue;
   const size_t shmem = (size_t)(n_req < GV_R ? n_req : GV_R) * K * sizeof(float);
   const int V = wdtype == DIT_BF16 ? GemvShape<bf16_t>::V : GemvShape<float>::V;
   int blocks = (N + 4 * V - 1) / (4 * V);
   if (blocks > 256 * 32) blocks = 256 * 32;
+  SetupArgs su{};
+  if (setup) su = *setup;
   for (int r0 = 0; r0 < n_req; r0 += GV_R) {
     const int nr = n_req - r0 < GV_R ? n_req - r0 : GV_R;
+    TimeArgs ta{};
+    if (act == GEMV_TIMESTEP)
+      for (int r = 0; r < nr; ++r) ta.t[r] = t_host[r0 + r];
+    const int sblocks = setup && r0 == 0 ? kSetupBlocks : 0;
+    const float* xr = x ? x + (long)r0 * ldx : nullptr;
+    float* yr = y + (long)r0 * ldy;
     if (wdtype == DIT_BF16)
-      gemv_dispatch<bf16_t>(blocks, shmem, s, W, b, x + (long)r0 * ldx, ldx, nr, K, N, act, y + (long)r0 * ldy, ldy);
+      gemv_dispatch<bf16_t>(K, blocks, sblocks, shmem, s, W, b, xr, ldx, nr, K, N, act, yr, ldy, ta, su);
     else
-      gemv_dispatch<float>(blocks, shmem, s, W, b, x + (long)r0 * ldx, ldx, nr, K, N, act, y + (long)r0 * ldy, ldy);
+      gemv_dispatch<float>(K, blocks, sblocks, shmem, s, W, b, xr, ldx, nr, K, N, act, yr, ldy, ta, su);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
@@ -386,8 +402,9 @@ hipError_t launch_euler(int dtype, void* x, const void* v, int channels, const B
 hipError_t launch_v_transpose(int dtype, const void* v, const BatchMeta& meta, int heads, int d, void* vt,
                               hipStream_t s) {
   const long ld = meta.pad_off[meta.n_req];
-  const dim3 grid((meta.T + 31) / 32, (d + 31) / 32, heads);
   if (meta.T == 0) return hipSuccess;
+  if (d % 64 != 0) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)(ld / 64), d / 64, heads);
   if (dtype == DIT_BF16)
     hipLaunchKernelGGL(v_transpose_kernel<bf16_t>, grid, dim3(256), 0, s, (const bf16_t*)v, meta, heads, d,
                        (bf16_t*)vt, ld);
