@@ -428,21 +428,29 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const AttnArgs a, const
 }
 
 // ----------------------------------------------------------------------------
-// fp32 attention (head_dim 64) for fp32 models: 64 queries per block, four
-// lanes per query (lane part p holds dims 16p .. 16p + 15 of q and O), K and V
-// tiles of 64 keys in LDS (rows of 16 float4, padded to 17 so the tile stores
-// of a wave spread over the banks), and the online softmax taken per tile in
-// fp32: all 64 scores of a tile (partial dot products summed over the quad),
-// one rescale of O and l, then O += P V.  exp2 of a log2(e)-scaled argument
-// adds one rounding of the argument (about 2e-6 relative at the scores met).
+// fp32 attention (head_dim 64) for fp32 models, on the fp32 matrix cores
+// (v_mfma_f32_16x16x4_f32: fp32 products and sums).  A block owns 16 queries of
+// a head; its four waves take the 16-key tiles in turn, each with its own
+// running max, sum and O, and the four results are merged at the end in wave
+// order.  A tile's scores are S^T = K Q^T, so a lane holds four keys of one
+// query; as in the bf16 kernel the probabilities feed O^T = V^T P^T from
+// registers: MFMA step r of a tile takes key 4 (lane / 16) + r from every lane
+// quarter, and V^T's 16-byte pieces hold the same keys (its middle quads are
+// swapped in memory).  K and V^T go straight from memory to registers, the
+// next tile's loads under this tile's MFMAs.  The small model's launches
+// (288 keys, 6 heads) are bound by latency: 108 blocks with 5 tiles per wave
+// instead of 30 blocks with 5 tiles of 64;
+// 13.4 us between events, launch included, against 98 us for four lanes per
+// query on the vector ALUs.  exp2 of a
+// log2(e)-scaled argument adds one rounding of the argument (about 2e-6
+// relative at the scores met).
 constexpr int FD = 64;
-constexpr int FQ = 64;
+constexpr int FQ = 16;
 
 __global__ __launch_bounds__(256) void attn_f32_kernel(const AttnArgs a, const AttnSched sc) {
-  constexpr int F4 = FD / 4;  // float4 per row
   constexpr float kLog2e = 1.4426950408889634f;
-  __shared__ float4 Ksh[64][F4 + 1];
-  __shared__ float4 Vsh[64][F4 + 1];
+  __shared__ float osh[4][FQ][FD + 4];
+  __shared__ float2 ml[4][FQ];  // running max (log2 domain) and sum
   const int per_head = sc.tile_off[sc.n];
   const int h = blockIdx.x / per_head;
   const int t = blockIdx.x - h * per_head;
@@ -451,104 +459,108 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(const AttnArgs a, const A
   const int r = sc.req[slot];
   const int q0 = (t - sc.tile_off[slot]) * FQ;
   const int L = a.meta.joint_off[r + 1] - a.meta.joint_off[r];
-  const int tid = threadIdx.x;
-  const int part = tid & 3;  // the quad of a query is four consecutive lanes of one wave
-  const int qrow = q0 + (tid >> 2);
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int lr = lane & 15, kq = lane >> 4;
 
   const float* Qg = (const float*)a.q + (long)a.qk_off[r] * a.q_tok + (long)h * a.q_head;
   const float* Kg = (const float*)a.k + (long)a.qk_off[r] * a.k_tok + (long)h * a.k_head;
   const float* Vg = (const float*)a.vt + (long)a.vt_off[r] + (long)h * a.vt_head;
 
-  float4 q[4], o[4];
+  // dims 16 c + 4 kq .. + 3 of query lr (rows past L repeat the last query)
+  float4 q[4];
 #pragma unroll
-  for (int c = 0; c < 4; ++c) {
-    q[c] = (qrow < L) ? *(const float4*)(Qg + (long)qrow * a.q_tok + 16 * part + 4 * c)
-                      : make_float4(0.f, 0.f, 0.f, 0.f);
-    o[c] = make_float4(0.f, 0.f, 0.f, 0.f);
-  }
-  const float sl2 = a.scale * kLog2e;
-  float m = -INFINITY, l = 0.f;  // m in the log2 domain
-  for (int kv0 = 0; kv0 < L; kv0 += 64) {
-    __syncthreads();
-    // Each operand's tile arrives as 4 float4 loads per thread, all in flight
-    // before the LDS stores.  K rows past L re-read row L - 1 (their scores are
-    // masked); V^T is read in slot order, 64 slots of the request's padded
-    // columns per d, and slot s holds key vt_slot(s) (an involution).
-    {
-      float4 tq[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int idx = tid + u * 256;
-        tq[u] = *(const float4*)(Kg + (long)min(kv0 + (idx >> 4), L - 1) * a.k_tok + (idx & 15) * 4);
-      }
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int idx = tid + u * 256;
-        Ksh[idx >> 4][idx & 15] = tq[u];
-      }
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int idx = tid + u * 256;
-        tq[u] = *(const float4*)(Vg + (long)(idx >> 4) * a.vt_d + kv0 + (idx & 15) * 4);
-      }
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int idx = tid + u * 256, c = idx >> 4, s0 = kv0 + (idx & 15) * 4;
-        ((float*)Vsh[vt_slot(s0) - kv0])[c] = tq[u].x;
-        ((float*)Vsh[vt_slot(s0 + 1) - kv0])[c] = tq[u].y;
-        ((float*)Vsh[vt_slot(s0 + 2) - kv0])[c] = tq[u].z;
-        ((float*)Vsh[vt_slot(s0 + 3) - kv0])[c] = tq[u].w;
-      }
-    }
-    __syncthreads();
-    const int nk = min(64, L - kv0);
-    float s[64];
-    float mx = m;
-#pragma unroll
-    for (int j = 0; j < 64; ++j) {
-      float d = 0.f;
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        const float4 k4 = Ksh[j][4 * part + c];
-        d = fmaf(q[c].x, k4.x, fmaf(q[c].y, k4.y, fmaf(q[c].z, k4.z, fmaf(q[c].w, k4.w, d))));
-      }
-      d += __shfl_xor(d, 1, 64);
-      d += __shfl_xor(d, 2, 64);
-      s[j] = j < nk ? d * sl2 : -INFINITY;
-      mx = fmaxf(mx, s[j]);
-    }
-    // mx is finite: the tile holds at least one key
-    const float al = exp2f(m - mx);
-    float ps = 0.f;
-#pragma unroll
-    for (int j = 0; j < 64; ++j) {
-      s[j] = exp2f(s[j] - mx);
-      ps += s[j];
-    }
-    l = l * al + ps;
-    m = mx;
+  for (int c = 0; c < 4; ++c) q[c] = *(const float4*)(Qg + (long)min(q0 + lr, L - 1) * a.q_tok + c * 16 + kq * 4);
+  // V^T row 16 c + lr, the four slots that hold keys 4 kq .. + 3 of a tile
+  const int vq = vt_slot(kq * 4);
+  const int nt = (L + 15) / 16;
+  float4 kf[2][4], vf[2][4];
+  auto load = [&](auto bufc, int j) __attribute__((always_inline)) {
+    constexpr int buf = decltype(bufc)::value;
+    const int jj = min(j, nt - 1);  // past the last tile: loaded again, not used
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
-      float4 acc = make_float4(o[c].x * al, o[c].y * al, o[c].z * al, o[c].w * al);
-#pragma unroll
-      for (int j = 0; j < 64; ++j) {
-        const float4 v = Vsh[j][4 * part + c];
-        acc.x = fmaf(s[j], v.x, acc.x);
-        acc.y = fmaf(s[j], v.y, acc.y);
-        acc.z = fmaf(s[j], v.z, acc.z);
-        acc.w = fmaf(s[j], v.w, acc.w);
-      }
-      o[c] = acc;
+      kf[buf][c] = *(const float4*)(Kg + (long)min(jj * 16 + lr, L - 1) * a.k_tok + c * 16 + kq * 4);
+      vf[buf][c] = *(const float4*)(Vg + (long)(c * 16 + lr) * a.vt_d + jj * 16 + vq);
     }
-  }
-  if (qrow < L) {
-    const int row = a.o_stream_major ? padded_to_row(a.meta, r, qrow) : a.meta.joint_off[r] + qrow;
-    float* og = (float*)a.o + (long)row * a.o_tok + (long)h * a.o_head + 16 * part;
-    const float inv = 1.0f / l;
+  };
+  auto at = [](const float4& v, auto ec) __attribute__((always_inline)) {
+    constexpr int e = decltype(ec)::value;
+    return e == 0 ? v.x : e == 1 ? v.y : e == 2 ? v.z : v.w;
+  };
+  const float sl2 = a.scale * kLog2e;
+  float m = -INFINITY, l = 0.f;  // m: of the query, in the log2 domain; l: of this lane's keys
+  f32x4_t o[4] = {};             // O^T rows 16 c + 4 kq .. + 3 of query lr
+  auto tile = [&](auto bufc, int j) __attribute__((always_inline)) {
+    constexpr int buf = decltype(bufc)::value;
+    // two chains of MFMAs: each result waits for the one before it
+    f32x4_t s0 = {}, s1 = {};
+#pragma unroll
+    for (int c = 0; c < 4; c += 2)
+      static_for<4>([&](auto ec) {
+        s0 = __builtin_amdgcn_mfma_f32_16x16x4f32(at(kf[buf][c], ec), at(q[c], ec), s0, 0, 0, 0);
+        s1 = __builtin_amdgcn_mfma_f32_16x16x4f32(at(kf[buf][c + 1], ec), at(q[c + 1], ec), s1, 0, 0, 0);
+      });
+    float s[4], mx = m;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      s[i] = j * 16 + kq * 4 + i < L ? (s0[i] + s1[i]) * sl2 : -INFINITY;
+      mx = fmaxf(mx, s[i]);
+    }
+    mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));  // finite: the tile holds at least one key
+    const float al = exp2f(m - mx);
+    m = mx;
+    l *= al;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      s[i] = exp2f(s[i] - mx);
+      l += s[i];
+    }
 #pragma unroll
     for (int c = 0; c < 4; ++c)
-      *(float4*)(og + 4 * c) = make_float4(o[c].x * inv, o[c].y * inv, o[c].z * inv, o[c].w * inv);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) o[c][i] *= al;
+    static_for<4>([&](auto ec) {
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+        o[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(at(vf[buf][c], ec), s[decltype(ec)::value], o[c], 0, 0, 0);
+    });
+  };
+  using B0 = std::integral_constant<int, 0>;
+  using B1 = std::integral_constant<int, 1>;
+  load(B0{}, wave);
+  for (int j = wave; j < nt; j += 8) {
+    load(B1{}, j + 4);
+    tile(B0{}, j);
+    load(B0{}, j + 8);
+    if (j + 4 < nt) tile(B1{}, j + 4);
   }
+  l += __shfl_xor(l, 16, 64);
+  l += __shfl_xor(l, 32, 64);
+  if (kq == 0) ml[wave][lr] = make_float2(m, l);
+#pragma unroll
+  for (int c = 0; c < 4; ++c) *(float4*)&osh[wave][lr][c * 16 + kq * 4] = make_float4(o[c][0], o[c][1], o[c][2], o[c][3]);
+  __syncthreads();
+  // 16 lanes per query, 4 dims each.  A wave without a tile has max -inf and
+  // weighs nothing; wave 0 always has one.
+  const int ql = tid >> 4, dd = (tid & 15) * 4, qrow = q0 + ql;
+  if (qrow >= L) return;
+  float mm = ml[0][ql].x;
+#pragma unroll
+  for (int w = 1; w < 4; ++w) mm = fmaxf(mm, ml[w][ql].x);
+  float ls = 0.f;
+  float4 y = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+  for (int w = 0; w < 4; ++w) {
+    const float wt = exp2f(ml[w][ql].x - mm);
+    const float4 v = *(const float4*)&osh[w][ql][dd];
+    ls = fmaf(wt, ml[w][ql].y, ls);
+    y = make_float4(fmaf(wt, v.x, y.x), fmaf(wt, v.y, y.y), fmaf(wt, v.z, y.z), fmaf(wt, v.w, y.w));
+  }
+  const float inv = 1.0f / ls;
+  const int row = a.o_stream_major ? padded_to_row(a.meta, r, qrow) : a.meta.joint_off[r] + qrow;
+  *(float4*)((float*)a.o + (long)row * a.o_tok + (long)h * a.o_head + dd) =
+      make_float4(y.x * inv, y.y * inv, y.z * inv, y.w * inv);
 }
 
 AttnSched make_sched(const BatchMeta& m, int bq) {

@@ -50,3 +50,21 @@ def test_step_width_not_a_multiple_of_the_wave_tile():
     assert "gemm_bf16_288x192" in ran, list(ran)
     ref = np.concatenate(_oracle_step(m, params, grids, n_txt, ts, lat, txt))
     assert normwise_err(vel.float().cpu().numpy(), ref) < BF16_TOL
+
+
+@pytest.mark.parametrize("M,N,K", [
+    (1, 1, 8), (33, 31, 24), (32, 32, 16), (65, 130, 72),   # K split over a block's waves: fewer chunks than waves, odd tails
+    (1024, 1024, 40), (1025, 1030, 264),                    # 256 and more 64x64 tiles: a wave each
+])
+def test_linear_f32_tiles(M, N, K):
+    """fp32 GEMM at the edges of its two tilings, without bias and with an output that is not 16-byte aligned;
+    K products of N(0, 1) x N(0, 0.02^2) summed in fp32: error below sqrt(K) 2^-23 of the sums' scale."""
+    import torch
+    x = synth.normal(13, "x", (M, K))
+    w = synth.normal(13, "w", (N, K), std=0.02)
+    ref = x.astype(np.float64) @ w.astype(np.float64).T
+    y = torch.full((M * N + 1,), float("nan"), dtype=torch.float32, device="cuda")
+    dit.dit_linear(M, N, K, dit.DIT_F32, to_dev(x, torch.float32), to_dev(w, torch.float32), None, y[1:], dit.DIT_F32)
+    torch.cuda.synchronize()
+    got = y[1:].cpu().numpy().reshape(M, N)
+    assert np.abs(got - ref).max() <= 2 ** -23 * np.sqrt(K) * 0.02 * np.sqrt(K) * 4 + 1e-9
