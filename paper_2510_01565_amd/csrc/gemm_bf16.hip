@@ -74,6 +74,10 @@ __device__ __forceinline__ void wait_vmcnt() {
 }
 
 typedef int i32x4_t __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+
+// cache policy of a buffer access at agent scope (sc1)
+constexpr int kAgentScope = 16;
 
 // Single instructions as volatile asm statements, which the compiler keeps in
 // the order written: a main loop built from them runs exactly its schedule.
@@ -779,65 +783,62 @@ __global__ __launch_bounds__(NWM* NWN * 64) void gemm_bf16_kernel(const GemmProb
       // of the tile to arrive -- add every piece's in piece order (the same
       // order whichever piece arrives last) and go on to the epilogue.  A
       // piece that finds all the others already counted skips publishing.
-      // Only thread 0 orders memory: every wave waits for its own stores
-      // before the block barrier, thread 0 then releases at agent scope
-      // (writing the XCD's L2 back) and counts, and only a block that reads
-      // the others' sums acquires (an acquire invalidates the L2 of its XCD,
-      // which blocks still multiplying there depend on).
-      constexpr int NV = AM * AN;
+      // The sums move by agent-scope accesses (sc1): stores write through the
+      // XCD's L2 and loads do not take lines it holds, so no block writes a
+      // whole L2 back or invalidates it under the blocks still multiplying
+      // there.  Every wave waits for its own stores before the block barrier,
+      // and thread 0 counts after it.  With a release fence per publishing and
+      // an acquire fence per merging block, and one load in flight at a time,
+      // the split cost 22 us of 100 on 768 x 3072 x 15360 (3 pieces) and 38 of
+      // 150 on 1536 x 3072 x 12288; now about half.
+      constexpr int NV = AM * AN, NB = NV % 8 == 0 ? 8 : NV % 6 == 0 ? 6 : 1;
       int* const flag = (int*)&lds[STAGES * STAGE - 1];  // past the epilogue's LDS (asserted below)
       int* const cnt = P.sk_cnt + tile_id;
-      float4* const slots = (float4*)P.sk_part + (long)tile_id * np * NV * NT;
-      if (tid == 0) {
-        const bool last = __hip_atomic_load(cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == np - 1;
-        if (last) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-        *flag = last;
-      }
+      auto slot = [&](int q) __attribute__((always_inline)) {
+        return __builtin_amdgcn_make_buffer_rsrc((char*)P.sk_part + ((long)tile_id * np + q) * (NV * NT * 16), (short)0,
+                                                 NV * NT * 16, kBufferWord3);
+      };
+      if (tid == 0) *flag = __hip_atomic_load(cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == np - 1;
       __syncthreads();
       if (!*flag) {
-        float4* const mine = slots + (long)piece * NV * NT;
+        const __amdgpu_buffer_rsrc_t mine = slot(piece);
 #pragma unroll
         for (int i = 0; i < AM; ++i)
 #pragma unroll
-          for (int j = 0; j < AN; ++j) {
-            const f32x4_t a4 = acc16[i][j];
-            mine[(i * AN + j) * NT + tid] = make_float4(a4[0], a4[1], a4[2], a4[3]);
-          }
-        // every wave's partial sums reach L2 before the barrier: the block
-        // barrier alone does not wait for other waves' stores, and thread 0's
-        // release below only waits for its own wave's
+          for (int j = 0; j < AN; ++j)
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, acc16[i][j]), mine, tid * 16,
+                                                   (i * AN + j) * NT * 16, kAgentScope);
         wait_vmcnt<0>();
         __syncthreads();
-        if (tid == 0) {
-          // release: the XCD's L2 written back, and the write-back complete,
-          // before the count
-          __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-          wait_vmcnt<0>();
-          const bool last = __hip_atomic_fetch_add(cnt, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == np - 1;
-          if (last) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-          *flag = last;
-        }
+        if (tid == 0) *flag = __hip_atomic_fetch_add(cnt, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == np - 1;
         __syncthreads();
         if (!*flag) return;  // uniform across the block
       }
+      // NB accumulators at a time, a piece's loads for all of them in flight together
+      static_for<NV / NB>([&](auto bc) {
+        constexpr int b0 = decltype(bc)::value * NB;
+        f32x4_t t[NB] = {};
+        for (int q = 0; q < np; ++q) {
+          if (q == piece) {
+            static_for<NB>([&](auto ec) {
+              constexpr int e = decltype(ec)::value, v = b0 + e;
+              t[e] += acc16[v / AN][v % AN];
+            });
+          } else {
+            const __amdgpu_buffer_rsrc_t r = slot(q);
+            u32x4_t w[NB];
 #pragma unroll
-      for (int i = 0; i < AM; ++i)
+            for (int e = 0; e < NB; ++e)
+              w[e] = __builtin_amdgcn_raw_buffer_load_b128(r, tid * 16, (b0 + e) * NT * 16, kAgentScope);
 #pragma unroll
-        for (int j = 0; j < AN; ++j) {
-          f32x4_t t = {0.f, 0.f, 0.f, 0.f};
-          for (int qq = 0; qq < np; ++qq) {
-            if (qq == piece) {
-              t += acc16[i][j];
-            } else {
-              const float4 v = slots[((long)qq * NV + i * AN + j) * NT + tid];
-              t[0] += v.x;
-              t[1] += v.y;
-              t[2] += v.z;
-              t[3] += v.w;
-            }
+            for (int e = 0; e < NB; ++e) t[e] += __builtin_bit_cast(f32x4_t, w[e]);
           }
-          acc16[i][j] = t;
         }
+        static_for<NB>([&](auto ec) {
+          constexpr int e = decltype(ec)::value, v = b0 + e;
+          acc16[v / AN][v % AN] = t[e];
+        });
+      });
       if (tid == 0) __hip_atomic_store(cnt, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
   } else {
