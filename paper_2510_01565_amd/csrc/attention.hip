@@ -62,8 +62,15 @@ __device__ __forceinline__ void wait_vmcnt0_lgkmcnt0() { __builtin_amdgcn_s_wait
 // Pipeline over key tiles j: K and V^T tiles arrive by direct-to-LDS buffer
 // loads in two stages, tile j + 1 loading while tile j runs scores, softmax
 // and P V in turn.
-template <int NW, int HD, int STAGES, int BKV>
-__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2)))
+//
+// KG = 2: two groups of NW waves share the block's queries and split its key
+// tiles into a first and a second half, each group with LDS stages of its
+// own; the second group hands its O, max and sum to the first through LDS at
+// the end.  For launches that leave CUs with one block or none: a lone block
+// of 4 waves runs its tiles one after the other at one wave per SIMD.
+template <int NW, int HD, int STAGES, int BKV, int KG>
+__global__ __launch_bounds__(NW * KG * 64)
+    __attribute__((amdgpu_waves_per_eu(HD == 64 ? (NW * KG == 8 ? 4 : 3) : 2)))
 void attn_bf16_kernel(const AttnArgs a, const AttnSched sc) {
   static_assert(STAGES == 2, "two LDS stages, the loop is unrolled over them");
   constexpr int BQ = NW * 32;
@@ -83,7 +90,7 @@ void attn_bf16_kernel(const AttnArgs a, const AttnSched sc) {
   // (an involution in c)
   auto kswz = [](int key, int c) { return HD == 128 ? c ^ (key & 15) : c ^ ((key >> 1) & 7); };
   auto vswz = [](int dr, int c) { return BKV == 128 ? c ^ (dr & 15) : c ^ ((dr >> 1) & 7); };
-  __shared__ uint4 smem[STAGES][KT_U4 + VT_U4];
+  __shared__ uint4 smem[KG * STAGES][KT_U4 + VT_U4];
 
   const int per_head = sc.tile_off[sc.n];
   // unit (query tile x head) of this block and, on a key-split launch, its
@@ -105,7 +112,9 @@ void attn_bf16_kernel(const AttnArgs a, const AttnSched sc) {
   const int q0 = (t - sc.tile_off[slot]) * BQ;
   const int L = a.meta.joint_off[r + 1] - a.meta.joint_off[r];
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int kg = KG == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid >> 6) / NW;  // key group
+  const int wave = (tid >> 6) - kg * NW;                                      // query wave
   const int hl = lane >> 5;  // lane half
 
   const bf16_t* __restrict__ Qg = (const bf16_t*)a.q + (long)a.qk_off[r] * a.q_tok + (long)h * a.q_head;
@@ -131,8 +140,8 @@ void attn_bf16_kernel(const AttnArgs a, const AttnSched sc) {
     vvo[q] = (dr * (int)a.vt_d + vswz(dr, lane % VCH) * 8) * 2;
   }
   const int wv = __builtin_amdgcn_readfirstlane(wave);
-  char* const lbase = (char*)&smem[0][0];
   constexpr int STAGE_B = (KT_U4 + VT_U4) * 16;
+  char* const lbase = (char*)&smem[0][0] + kg * STAGES * STAGE_B;
   auto tile_load = [&](int j, auto stc) __attribute__((always_inline)) {
     constexpr int st = decltype(stc)::value;
     const int kv0 = j * BKV;
@@ -158,11 +167,14 @@ void attn_bf16_kernel(const AttnArgs a, const AttnSched sc) {
 
   // key tiles [jb, je) of this block (all of them unless the keys are split)
   const int nt_all = (L + BKV - 1) / BKV;
-  const int jb = piece * nt_all / a.kv_pieces;
-  const int je = (piece + 1) * nt_all / a.kv_pieces;
+  const int jb0 = piece * nt_all / a.kv_pieces;
+  const int je0 = (piece + 1) * nt_all / a.kv_pieces;
+  // this group's share: the first half, rounded up, or the rest
+  const int half = (je0 - jb0 + KG - 1) / KG;
+  const int jb = jb0 + kg * half, je = KG == 1 ? je0 : min(jb + half, je0);
   using S0 = std::integral_constant<int, 0>;
   using S1 = std::integral_constant<int, 1>;
-  tile_load(jb, S0{});
+  if (KG == 1 || jb < je) tile_load(jb, S0{});
 
   // Q fragments (B operand of S^T = K Q^T): query q0 + wave*32 + lane%32, d chunk 2*ks + lane/32
   const int qrow = q0 + wave * 32 + (lane & 31);
@@ -332,6 +344,34 @@ void attn_bf16_kernel(const AttnArgs a, const AttnSched sc) {
   if (j < je) {
     if (((j - jb) & 1) == 0) step(j, S0{}, Mask{});
     else step(j, S1{}, Mask{});
+  }
+  if constexpr (KG > 1) {
+    // at most one tile fewer in the second group, which still meets the barrier
+    if (je - jb < half) asm volatile("s_barrier" ::: "memory");
+    // the groups' results meet as [wave][register][lane] in LDS, whose tiles
+    // nobody reads any more
+    constexpr int NR = HD / 2;  // O registers of a lane
+    float* const sh = (float*)&smem[0][0] + (wave * (NR + 2)) * 64 + lane;
+    static_assert(NW * (NR + 2) * 64 * 4 <= (int)sizeof(smem), "merge LDS");
+    if (kg == 1) {
+#pragma unroll
+      for (int db = 0; db < HD / 32; ++db)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) sh[(db * 16 + i) * 64] = o[db][i];
+      sh[NR * 64] = m_i;
+      sh[(NR + 1) * 64] = l_i;
+    }
+    __syncthreads();
+    if (kg == 1) return;
+    // a group without a tile has max -inf, sum 0 and O 0
+    const float m1 = sh[NR * 64], mm = fmaxf(m_i, m1);
+    const float a0 = __builtin_amdgcn_exp2f(m_i - mm), a1 = __builtin_amdgcn_exp2f(m1 - mm);
+    m_i = mm;
+    l_i = l_i * a0 + sh[(NR + 1) * 64] * a1;
+#pragma unroll
+    for (int db = 0; db < HD / 32; ++db)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) o[db][i] = o[db][i] * a0 + sh[(db * 16 + i) * 64] * a1;
   }
 
   const float l = l_i + __shfl_xor(l_i, 32, 64);
@@ -596,7 +636,7 @@ AttnSched make_sched(const BatchMeta& m, int bq) {
 constexpr int kKeyTile = 64;
 static_assert(kSeqPad % kKeyTile == 0, "V^T padding");
 
-template <int NW, int HD>
+template <int NW, int HD, int KG = 1>
 hipError_t launch_attn_cfg(const AttnArgs& a, hipStream_t s) {
   const AttnSched sc = make_sched(a.meta, NW * 32);
   const long blocks = (long)sc.tile_off[sc.n] * a.heads;
@@ -605,7 +645,8 @@ hipError_t launch_attn_cfg(const AttnArgs& a, hipStream_t s) {
   b.unit0 = 0;
   b.units = (int)blocks;
   b.kv_pieces = 1;
-  hipLaunchKernelGGL((attn_bf16_kernel<NW, HD, 2, kKeyTile>), dim3((unsigned)blocks), dim3(NW * 64), 0, s, b, sc);
+  hipLaunchKernelGGL((attn_bf16_kernel<NW, HD, 2, kKeyTile, KG>), dim3((unsigned)blocks), dim3(NW * KG * 64), 0, s, b,
+                     sc);
   return hipGetLastError();
 }
 
@@ -677,9 +718,28 @@ size_t split_bytes(const SplitPlan& p, int head_dim) {
 // -0.9%.  The rule assumes equal units, i.e. requests of one length; for a
 // batch of mixed lengths (longest first, so the last round holds the short
 // units) the 128-query blocks are kept (the packed 256-2048 px step: +0.6%
-// with 256-query blocks).  At head dim 64 (half the registers, so two
-// 256-query blocks fit on a CU) the 256-query blocks stay ahead until the
-// launch has 2048 units.
+// with 256-query blocks).
+//
+// At head dim 64 the softmax's vector work is the longer half of a tile, and
+// more waves per SIMD fill it: 128-query blocks run three per CU (155 VGPRs, 768
+// slots), 256-query blocks two (held to 128 VGPRs, 512 slots; one per CU at
+// 153).  wide_64() compares the two by their rounds, in units of the time a
+// lone 128-query block takes for 1.3 times its keys, as measured at 1 792 -
+// 16 717 tokens and 3 - 24 heads: a full round costs 1.6 (768 units) and 1.95
+// (512 blocks), and the last round 0.4 / 0.87 / 1.36 for up to 1 / 2 / 3
+// 128-query blocks per CU and 0.9 / 1.76 for up to 1 / 2 256-query blocks.  Up
+// to 768 units the 128-query blocks are never slower.  Against one 256-query
+// block per CU at every size: 210 units 75 -> 53 us, 528 101 -> 76, 840
+// 154 -> 143, 1584 566 -> 481, 3144 1737 -> 1735; a packed batch of 589, 1357 and
+// 4429 tokens (12 heads) 148 -> 110.
+bool wide_64(long units, long units8) {
+  if (units <= 768) return false;
+  static const double narrow_last[] = {0.0, 0.4, 0.87, 1.36}, wide_last[] = {0.0, 0.9, 1.76};
+  const double narrow = 0.2 + 1.6 * (double)(units / 768) + narrow_last[(units % 768 + 255) / 256];
+  const double wide = 0.25 + 1.95 * (double)(units8 / 512) + wide_last[(units8 % 512 + 255) / 256];
+  return wide < narrow;
+}
+
 template <int HD>
 hipError_t launch_attn_hd(const AttnArgs& a, hipStream_t s) {
   const SplitPlan sp = a.split_buf ? split_plan(a.meta, a.heads, HD) : SplitPlan{0, 0, 0};
@@ -689,32 +749,33 @@ hipError_t launch_attn_hd(const AttnArgs& a, hipStream_t s) {
     b.unit0 = 0;
     b.units = sp.main_units;
     b.kv_pieces = 1;
-    hipLaunchKernelGGL((attn_bf16_kernel<4, HD, 2, kKeyTile>), dim3((unsigned)sp.main_units), dim3(256), 0, s, b, sc);
+    hipLaunchKernelGGL((attn_bf16_kernel<4, HD, 2, kKeyTile, 1>), dim3((unsigned)sp.main_units), dim3(256), 0, s, b, sc);
     b.unit0 = sp.main_units;
     b.units = sp.tail_units;
     b.kv_pieces = sp.pieces;
-    hipLaunchKernelGGL((attn_bf16_kernel<4, HD, 2, kKeyTile>), dim3((unsigned)(sp.tail_units * sp.pieces)), dim3(256), 0, s, b,
+    hipLaunchKernelGGL((attn_bf16_kernel<4, HD, 2, kKeyTile, 1>), dim3((unsigned)(sp.tail_units * sp.pieces)), dim3(256), 0, s, b,
                        sc);
     hipLaunchKernelGGL((attn_merge_kernel<HD>), dim3((unsigned)sp.tail_units), dim3(256), 0, s, b, sc);
     return hipGetLastError();
   }
   const AttnSched sc4 = make_sched(a.meta, 4 * 32);
   const long units = (long)sc4.tile_off[sc4.n] * a.heads;
-  bool wide;
-  if (HD == 128) {
-    bool equal = true;
-    const int L0 = a.meta.joint_off[sc4.req[0] + 1] - a.meta.joint_off[sc4.req[0]];
-    for (int i = 1; i < sc4.n; ++i)
-      equal = equal && a.meta.joint_off[sc4.req[i] + 1] - a.meta.joint_off[sc4.req[i]] == L0;
-    // fill of the 256-query launch's own last round (its block count is not
-    // units / 2 when a request has an odd number of 128-query tiles)
-    const AttnSched sc8 = make_sched(a.meta, 8 * 32);
-    const long units8 = (long)sc8.tile_off[sc8.n] * a.heads;
-    constexpr long kSlots8 = 256;  // 256-query blocks resident per GPU (one per CU)
-    wide = equal && 2 * (units8 % kSlots8) > kSlots8;
-  } else {
-    wide = units < 2048;
-  }
+  bool equal = true;
+  const int L0 = a.meta.joint_off[sc4.req[0] + 1] - a.meta.joint_off[sc4.req[0]];
+  for (int i = 1; i < sc4.n; ++i)
+    equal = equal && a.meta.joint_off[sc4.req[i] + 1] - a.meta.joint_off[sc4.req[i]] == L0;
+  // the 256-query launch's own block count (not units / 2 when a request has
+  // an odd number of 128-query tiles) and the fill of its last round
+  const AttnSched sc8 = make_sched(a.meta, 8 * 32);
+  const long units8 = (long)sc8.tile_off[sc8.n] * a.heads;
+  constexpr long kSlots8 = 256;  // 256-query blocks resident per GPU at head dim 128 (one per CU)
+  const bool wide = equal && (HD == 128 ? 2 * (units8 % kSlots8) > kSlots8 : wide_64(units, units8));
+  // Two key groups per block where every block has a CU to itself and at least
+  // 20 key tiles: 168 units x 28 tiles 62.6 -> 52.2 us at head dim 128 and 42.6
+  // -> 36.9 at 64, 240 x 40 88.7 -> 81.4 and 57.5 -> 51.6, 240 x 20 32.2 -> 31.1
+  // and 21.9 -> 21.3; equal at 12 tiles and up to 12% slower below (the second
+  // group's tiles and the merge), equal or slower with more than 256 units.
+  if (a.allow_split && units <= 256 && L0 >= 20 * kKeyTile) return launch_attn_cfg<4, HD, 2>(a, s);
   if (wide) return launch_attn_cfg<8, HD>(a, s);
   return launch_attn_cfg<4, HD>(a, s);
 }

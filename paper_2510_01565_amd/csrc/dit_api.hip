@@ -509,6 +509,7 @@ hipError_t attention(const Ctx& x) {
   a.meta = x.meta;
   // the split GEMMs' partial-sum slots double as the attention's key-split
   // scratch (the two never run at once); null in batch-invariant mode
+  a.allow_split = !(x.c->flags & DIT_FLAG_BATCH_INVARIANT);
   if (x.ws.sk_part && attn_split_bytes(x.meta, a.heads, a.head_dim) <= (size_t)kSplitPartBytes)
     a.split_buf = x.ws.sk_part;
   return attn_launch(x.s, x.c->dtype, a);
@@ -957,6 +958,7 @@ dit_status dit_attention(const dit_batch* batch, int heads, int head_dim, int dt
     a.vt_off[r] = m.pad_off[r];
   }
   a.meta = m;
+  a.allow_split = 1;
   if (dtype == DIT_BF16 && attn_split_bytes(m, heads, head_dim) > 0)
     a.split_buf = (float*)((char*)ws + align256((size_t)heads * head_dim * Tp * elem_size(dtype)));
   HIP_TRY(attn_launch(s, dtype, a));

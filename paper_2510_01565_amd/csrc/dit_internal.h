@@ -180,6 +180,8 @@ struct AttnArgs {
   // attn_split_bytes(meta, heads, head_dim) bytes, or null (never split; the
   // output bits then do not depend on how many other tiles share the launch).
   float* split_buf;
+  // whether the order of a query's sums may depend on how many tiles the launch has
+  int allow_split;
   // set by the launcher: this launch covers query-tile units
   // [unit0, unit0 + units); kv_pieces > 1 splits each unit's keys into that
   // many ranges whose unnormalised partial results go to split_buf
