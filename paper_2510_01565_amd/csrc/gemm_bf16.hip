@@ -1022,17 +1022,27 @@ struct TileModel {
 // step the two tie on FLOPs per tile and 256x128 measured faster wherever the
 // two competed (M 768 .. 6144, the 256 / 512 px and SD3-shaped steps 0.7 - 2.4%
 // faster, the rest unchanged).
+// 256x256's rate is its fitted 7.31 raised by the 5% that its turn-taking
+// schedule gained on one-round launches.  Launches of more than one round hold
+// 256 busy CUs long enough for power to set the clock, and there the 256x128
+// and 128x256 tiles, which move 1.5 times the operand bytes per FLOP, fall
+// further behind than their one-round rates say (7622 x 3072 x 12288 inside a
+// step: 540 us in 3 rounds of 256x128, 500 us in 2 of 256x256): kSustainedLoss.
+// With both, one single block at 1024 px 1064 -> 1051 us (linear2 on 256x256
+// instead of 288x192), a packed 7622-row double block 1991 -> 1948 us, the
+// 57-block 1024 px step 63.4 -> 63.0 ms, other sizes unchanged.
 // 288x192 (12 waves of 96x48) divides 4608 x 3072 into exactly 256 tiles;
 // its rate is set from the same large shapes on which 256x256 was measured
 // (0.915 of 256x256's when both fill the GPU).  It is considered only for
 // launches it covers in one round (see pick).
 constexpr TileModel kTileModels[] = {
-    {CFG_256x256, 256, 256, 7.31, 11.7},
+    {CFG_256x256, 256, 256, 7.7, 11.7},
     {CFG_256x128, 256, 128, 6.23, 8.4},
     {CFG_128x256, 128, 256, 6.23, 8.7},
     {CFG_128x128, 128, 128, 5.07, 4.1},
     {CFG_288x192, 288, 192, 6.31, 8.0},
 };
+constexpr double kSustainedLoss = 1.07;
 // Split K: the merge adds, on the critical path, the write of a piece's
 // partial sums and the last piece's read of the others' (fp32, bm x bn per
 // piece) plus the arrival handshake.  A split is taken only when the model
@@ -1054,6 +1064,7 @@ double model_us(const TileModel& t, const GemmProblem& p, int sk) {
   if (tiles == 0) return 0.0;
   const long units = tiles * sk;
   double us = (double)((units + 255) / 256) * (work / units);
+  if (units > 256 && (t.cfg == CFG_256x128 || t.cfg == CFG_128x256)) us *= kSustainedLoss;
   if (sk > 1) us += kMergeFixedUs + (sk - 1) * 4.0 * t.bm * t.bn / kMergeBytesPerUs;
   return us;
 }
