@@ -335,7 +335,19 @@ hipError_t launch_gemv(int wdtype, const void* W, const void* b, const float* x,
   const size_t shmem = (size_t)(n_req < GV_R ? n_req : GV_R) * K * sizeof(float);
   const int V = wdtype == DIT_BF16 ? GemvShape<bf16_t>::V : GemvShape<float>::V;
   int blocks = (N + 4 * V - 1) / (4 * V);
-  if (blocks > 256 * 32) blocks = 256 * 32;
+  // Three blocks per CU are resident.  Launches of a few such rounds take one
+  // round of blocks that loop evenly instead: each new block waits for its
+  // activations before it asks for weights (36 864 rows of 3072 in bf16: 2304
+  // blocks 59 us between events, 768 blocks of 3 rounds 50).  Longer launches
+  // hide that wait (1.05 M rows: 8192 blocks 0.97 ms, 768 blocks 1.00), and
+  // below two rounds the loop would leave CUs idle (1152 blocks 20.7, 768 23.0).
+  constexpr int kResident = 3 * 256, kMaxBlocks = 256 * 32;
+  if (blocks > kMaxBlocks) {
+    blocks = kMaxBlocks;
+  } else if (blocks > 2 * kResident) {
+    const int rounds = (blocks + kResident - 1) / kResident;
+    blocks = (blocks + rounds - 1) / rounds;
+  }
   SetupArgs su{};
   if (setup) su = *setup;
   for (int r0 = 0; r0 < n_req; r0 += GV_R) {
