@@ -68,10 +68,14 @@ __device__ __forceinline__ void wait_vmcnt0_lgkmcnt0() { __builtin_amdgcn_s_wait
 // own; the second group hands its O, max and sum to the first through LDS at
 // the end.  For launches that leave CUs with one block or none: a lone block
 // of 4 waves runs its tiles one after the other at one wave per SIMD.
+//
+// attn_unit: the block's work on query tile q0 of head h of request r against
+// key tiles [jb0, je0).  part < 0: all keys, O is written; otherwise its
+// unnormalised O, maxima and sums go to slot `part` of the `parts` in
+// a.split_buf.  smem: KG * STAGES tile pairs, free again when it returns.
 template <int NW, int HD, int STAGES, int BKV, int KG>
-__global__ __launch_bounds__(NW * KG * 64)
-    __attribute__((amdgpu_waves_per_eu(HD == 64 ? (NW * KG == 8 ? 4 : 3) : 2)))
-void attn_bf16_kernel(const AttnArgs a, const AttnSched sc) {
+__device__ __forceinline__ void attn_unit(const AttnArgs& a, char* smem, int r, int h, int q0, int jb0, int je0,
+                                          int part, int parts) {
   static_assert(STAGES == 2, "two LDS stages, the loop is unrolled over them");
   constexpr int BQ = NW * 32;
   static_assert(HD == 64 || HD == 128, "head dim");
@@ -90,26 +94,6 @@ void attn_bf16_kernel(const AttnArgs a, const AttnSched sc) {
   // (an involution in c)
   auto kswz = [](int key, int c) { return HD == 128 ? c ^ (key & 15) : c ^ ((key >> 1) & 7); };
   auto vswz = [](int dr, int c) { return BKV == 128 ? c ^ (dr & 15) : c ^ ((dr >> 1) & 7); };
-  __shared__ uint4 smem[KG * STAGES][KT_U4 + VT_U4];
-
-  const int per_head = sc.tile_off[sc.n];
-  // unit (query tile x head) of this block and, on a key-split launch, its
-  // key range: blocks of one XCD take consecutive indices, and a split
-  // launch numbers the pieces key range first, so the blocks of one XCD
-  // share K/V ranges
-  const int bid = xcd_remap(blockIdx.x, gridDim.x);
-  int piece = 0, id = bid;
-  if (a.kv_pieces > 1) {
-    piece = bid / a.units;
-    id = bid - piece * a.units;
-  }
-  id += a.unit0;
-  const int h = id / per_head;
-  const int t = id - h * per_head;
-  int slot = 0;
-  while (slot + 1 < sc.n && t >= sc.tile_off[slot + 1]) ++slot;
-  const int r = sc.req[slot];
-  const int q0 = (t - sc.tile_off[slot]) * BQ;
   const int L = a.meta.joint_off[r + 1] - a.meta.joint_off[r];
 
   const int tid = threadIdx.x, lane = tid & 63;
@@ -141,7 +125,7 @@ void attn_bf16_kernel(const AttnArgs a, const AttnSched sc) {
   }
   const int wv = __builtin_amdgcn_readfirstlane(wave);
   constexpr int STAGE_B = (KT_U4 + VT_U4) * 16;
-  char* const lbase = (char*)&smem[0][0] + kg * STAGES * STAGE_B;
+  char* const lbase = smem + kg * STAGES * STAGE_B;
   auto tile_load = [&](int j, auto stc) __attribute__((always_inline)) {
     constexpr int st = decltype(stc)::value;
     const int kv0 = j * BKV;
@@ -165,10 +149,7 @@ void attn_bf16_kernel(const AttnArgs a, const AttnSched sc) {
     }
   };
 
-  // key tiles [jb, je) of this block (all of them unless the keys are split)
   const int nt_all = (L + BKV - 1) / BKV;
-  const int jb0 = piece * nt_all / a.kv_pieces;
-  const int je0 = (piece + 1) * nt_all / a.kv_pieces;
   // this group's share: the first half, rounded up, or the rest
   const int half = (je0 - jb0 + KG - 1) / KG;
   const int jb = jb0 + kg * half, je = KG == 1 ? je0 : min(jb + half, je0);
@@ -351,8 +332,8 @@ void attn_bf16_kernel(const AttnArgs a, const AttnSched sc) {
     // the groups' results meet as [wave][register][lane] in LDS, whose tiles
     // nobody reads any more
     constexpr int NR = HD / 2;  // O registers of a lane
-    float* const sh = (float*)&smem[0][0] + (wave * (NR + 2)) * 64 + lane;
-    static_assert(NW * (NR + 2) * 64 * 4 <= (int)sizeof(smem), "merge LDS");
+    float* const sh = (float*)smem + (wave * (NR + 2)) * 64 + lane;
+    static_assert(NW * (NR + 2) * 64 * 4 <= KG * STAGES * STAGE_B, "merge LDS");
     if (kg == 1) {
 #pragma unroll
       for (int db = 0; db < HD / 32; ++db)
@@ -375,10 +356,10 @@ void attn_bf16_kernel(const AttnArgs a, const AttnSched sc) {
   }
 
   const float l = l_i + __shfl_xor(l_i, 32, 64);
-  if (a.kv_pieces > 1) {
-    // one key range: O unnormalised, with its max m_i and sum l (every range
-    // holds at least one key, so both are finite), for attn_merge_kernel
-    const long qs = (long)bid * BQ + wave * 32 + (lane & 31);  // query slot
+  if (part >= 0) {
+    // a key range: O unnormalised, with its max m_i and sum l (every range
+    // holds at least one key, so both are finite), for the merge
+    const long qs = (long)part * BQ + wave * 32 + (lane & 31);  // query slot
     float* po = a.split_buf + qs * HD;
 #pragma unroll
     for (int db = 0; db < HD / 32; ++db)
@@ -387,7 +368,7 @@ void attn_bf16_kernel(const AttnArgs a, const AttnSched sc) {
         *(float4*)(po + db * 32 + g * 8 + hl * 4) =
             make_float4(o[db][g * 4 + 0], o[db][g * 4 + 1], o[db][g * 4 + 2], o[db][g * 4 + 3]);
     if (hl == 0) {
-      float2* pml = (float2*)(a.split_buf + (long)a.units * a.kv_pieces * BQ * HD);
+      float2* pml = (float2*)(a.split_buf + (long)parts * BQ * HD);
       pml[qs] = make_float2(m_i, l);
     }
     return;
@@ -406,6 +387,162 @@ void attn_bf16_kernel(const AttnArgs a, const AttnSched sc) {
         w.y = pack_bf16x2(o[db][g * 4 + 2] * inv, o[db][g * 4 + 3] * inv);
         *(uint2*)(og + dd) = w;
       }
+  }
+}
+
+template <int NW, int HD, int STAGES, int BKV, int KG>
+__global__ __launch_bounds__(NW * KG * 64)
+    __attribute__((amdgpu_waves_per_eu(HD == 64 ? (NW * KG == 8 ? 4 : 3) : 2)))
+void attn_bf16_kernel(const AttnArgs a, const AttnSched sc) {
+  __shared__ uint4 smem[KG * STAGES * BKV * HD / 4];  // [stage][K tile | V^T tile]
+  const int per_head = sc.tile_off[sc.n];
+  // unit (query tile x head) of this block and, on a key-split launch, its
+  // key range: blocks of one XCD take consecutive indices, and a split
+  // launch numbers the pieces key range first, so the blocks of one XCD
+  // share K/V ranges
+  const int bid = xcd_remap(blockIdx.x, gridDim.x);
+  int piece = 0, id = bid;
+  if (a.kv_pieces > 1) {
+    piece = bid / a.units;
+    id = bid - piece * a.units;
+  }
+  id += a.unit0;
+  const int h = id / per_head;
+  const int t = id - h * per_head;
+  int slot = 0;
+  while (slot + 1 < sc.n && t >= sc.tile_off[slot + 1]) ++slot;
+  const int r = sc.req[slot];
+  const int nt = (a.meta.joint_off[r + 1] - a.meta.joint_off[r] + BKV - 1) / BKV;
+  attn_unit<NW, HD, STAGES, BKV, KG>(a, (char*)smem, r, h, (t - sc.tile_off[slot]) * NW * 32,
+                                     piece * nt / a.kv_pieces, (piece + 1) * nt / a.kv_pieces,
+                                     a.kv_pieces > 1 ? bid : -1, a.units * a.kv_pieces);
+}
+
+// ---- Evenly shared key tiles.  Query tiles of 256 come in whole rounds of one
+// per CU only for few shapes, and a last round that is not full costs a whole
+// tile's time (16 896 tokens, 6 heads: 396 tiles in 2 rounds, 77% of them
+// filled).  Here the first rounds run as whole tiles, and every key tile of the
+// others is one step of a line (groups of equally long requests, longest
+// first; in a group head by head, tile by tile) that kStreamBlocks blocks cut
+// into equal runs.  A run holds the end of one query tile, whole tiles, and the
+// beginning of another: the whole ones are written, the two ends go to slots
+// 2 b and 2 b + 1, and a second kernel adds each cut tile's parts in key order.
+constexpr int kStreamBlocks = 256;
+struct AttnStream {
+  int n_groups;
+  int slot0[kMaxReq + 1];  // requests (AttnSched slots) of each group
+  int skip;                // whole tiles of group 0 that ran before
+  int steps, run;          // key tiles in all, and per block
+};
+
+// where step s of the line falls: query tile (group, unit) and the line's steps [begin, end) of that tile
+struct StreamAt {
+  int group, unit, begin, end;
+};
+__device__ __forceinline__ StreamAt stream_at(const AttnArgs& a, const AttnSched& sc, const AttnStream& st, int bkv,
+                                              int s) {
+  StreamAt at;
+  int base = 0;
+  for (int g = 0;; ++g) {
+    const int r = sc.req[st.slot0[g]];
+    const int nt = (a.meta.joint_off[r + 1] - a.meta.joint_off[r] + bkv - 1) / bkv;
+    const int skip = g == 0 ? st.skip : 0;
+    const int units = a.heads * (sc.tile_off[st.slot0[g + 1]] - sc.tile_off[st.slot0[g]]) - skip;
+    if (g + 1 == st.n_groups || s < base + units * nt) {
+      const int u = (s - base) / nt;
+      at.group = g;
+      at.unit = u + skip;
+      at.begin = base + u * nt;
+      at.end = at.begin + nt;
+      return at;
+    }
+    base += units * nt;
+  }
+}
+// request, head and first query of a unit
+__device__ __forceinline__ void stream_unit(const AttnSched& sc, const AttnStream& st, const StreamAt& at, int bq,
+                                            int& r, int& h, int& q0) {
+  const int t0 = sc.tile_off[st.slot0[at.group]], per_head = sc.tile_off[st.slot0[at.group + 1]] - t0;
+  h = at.unit / per_head;
+  const int t = t0 + at.unit - h * per_head;
+  int slot = st.slot0[at.group];
+  while (slot + 1 < st.slot0[at.group + 1] && t >= sc.tile_off[slot + 1]) ++slot;
+  r = sc.req[slot];
+  q0 = (t - sc.tile_off[slot]) * bq;
+}
+
+template <int HD, int BKV>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2)))
+void attn_stream_kernel(const AttnArgs a, const AttnSched sc, const AttnStream st) {
+  constexpr int NW = 8;
+  __shared__ uint4 smem[2 * BKV * HD / 4];
+  const int b = xcd_remap(blockIdx.x, gridDim.x);
+  const int s0 = b * st.run, s1 = min(s0 + st.run, st.steps);
+#pragma unroll 1
+  for (int s = s0; s < s1;) {
+    const StreamAt at = stream_at(a, sc, st, BKV, s);
+    const int e = min(at.end, s1);
+    int r, h, q0;
+    stream_unit(sc, st, at, NW * 32, r, h, q0);
+    const bool whole = s == at.begin && e == at.end;
+    attn_unit<NW, HD, 2, BKV, 1>(a, (char*)smem, r, h, q0, s - at.begin, e - at.begin,
+                                 whole ? -1 : s == s0 ? 2 * b : 2 * b + 1, 2 * kStreamBlocks);
+    s = e;
+  }
+}
+
+// Adds the parts of the query tile that the start of run blockIdx.x + 1 cuts
+// (nothing to do if it cuts none, or if an earlier run's start cuts the same
+// tile): O = sum_p 2^(m_p - M) O_p / sum_p 2^(m_p - M) l_p in key order.  64
+// queries per block, four threads per query.
+template <int HD, int BKV>
+__global__ __launch_bounds__(256) void attn_stream_merge_kernel(const AttnArgs a, const AttnSched sc,
+                                                                const AttnStream st) {
+  constexpr int BQ = 256, DH = HD / 4;
+  const int b1 = blockIdx.x + 1, cut = b1 * st.run;
+  if (cut >= st.steps) return;
+  const StreamAt at = stream_at(a, sc, st, BKV, cut);
+  if (at.begin == cut || at.begin < cut - st.run) return;
+  // a start at the tile's own first step does not cut it: the run before b1 is
+  // the first with a part (its last segment, or its only one)
+  int r, h, q0;
+  stream_unit(sc, st, at, BQ, r, h, q0);
+  const int ql = blockIdx.y * 64 + (threadIdx.x >> 2), dd = (threadIdx.x & 3) * DH;
+  const int qrow = q0 + ql, L = a.meta.joint_off[r + 1] - a.meta.joint_off[r];
+  if (qrow >= L) return;
+  const int bb = b1 - 1, be = (at.end - 1) / st.run;
+  // run p's part: its first segment (slot 2 p) if the tile began at or before the run did
+  auto slot = [&](int p) { return (long)(2 * p + (at.begin <= p * st.run ? 0 : 1)) * BQ + ql; };
+  const float2* pml = (const float2*)(a.split_buf + 2L * kStreamBlocks * BQ * HD);
+  float M = -INFINITY;
+  for (int p = bb; p <= be; ++p) M = fmaxf(M, pml[slot(p)].x);
+  float acc[DH] = {}, lsum = 0.f;
+  for (int p = bb; p <= be; ++p) {
+    const long qs = slot(p);
+    const float2 ml = pml[qs];
+    const float w = exp2f(ml.x - M);
+    lsum = fmaf(w, ml.y, lsum);
+    const float4* src = (const float4*)(a.split_buf + qs * HD + dd);
+#pragma unroll
+    for (int c = 0; c < DH / 4; ++c) {
+      const float4 v = src[c];
+      acc[4 * c + 0] = fmaf(w, v.x, acc[4 * c + 0]);
+      acc[4 * c + 1] = fmaf(w, v.y, acc[4 * c + 1]);
+      acc[4 * c + 2] = fmaf(w, v.z, acc[4 * c + 2]);
+      acc[4 * c + 3] = fmaf(w, v.w, acc[4 * c + 3]);
+    }
+  }
+  const float inv = 1.0f / lsum;
+  const int row = a.o_stream_major ? padded_to_row(a.meta, r, qrow) : a.meta.joint_off[r] + qrow;
+  bf16_t* og = (bf16_t*)a.o + (long)row * a.o_tok + (long)h * a.o_head + dd;
+#pragma unroll
+  for (int c = 0; c < DH / 8; ++c) {
+    uint4 w;
+    w.x = pack_bf16x2(acc[8 * c + 0] * inv, acc[8 * c + 1] * inv);
+    w.y = pack_bf16x2(acc[8 * c + 2] * inv, acc[8 * c + 3] * inv);
+    w.z = pack_bf16x2(acc[8 * c + 4] * inv, acc[8 * c + 5] * inv);
+    w.w = pack_bf16x2(acc[8 * c + 6] * inv, acc[8 * c + 7] * inv);
+    *(uint4*)(og + 8 * c) = w;
   }
 }
 
@@ -690,6 +827,69 @@ SplitPlan split_plan(const BatchMeta& m, int heads, int head_dim) {
   return p;
 }
 
+// The plan of evenly shared key tiles: R whole rounds, then equal runs.  It is
+// taken where it is modelled 2% below what the launch would otherwise be, in
+// steps (one key tile of a 256-query block on a full GPU, 1.67 us), from
+// timings at 1 357 - 16 896 tokens and 3 - 24 heads:
+//  shared out: a tile of n keys costs n + 4, and a run 28 more than its length
+//  (its two ends written and merged);
+//  256-query tiles in rounds: the last round, at most as long as a full one,
+//  costs 0.35 + 0.75 of its fill (power lets fewer busy CUs run faster), 0.9
+//  of that if it is the only one;
+//  128-query blocks: they share out by themselves, but their K / V^T tiles serve
+//  half the queries, 1.07 + 8 / n of the even share.
+// Against the launch used otherwise (us, 24 heads unless said): 16 896 tokens
+// 3017 -> 2810, 12 heads 1550 -> 1436, 6 heads 769 -> 749; 8 612 tokens 851 ->
+// 797; 768 + 1 536 + 4 608 + 16 896 tokens 3313 -> 3186.  Not taken: 4 608 tokens
+// (equal), 8 612 with 12 heads (2% slower), 16 896 with 3 heads (4% slower).
+struct StreamPlan {
+  AttnSched sc;
+  AttnStream st;
+  int main_units;
+};
+
+size_t stream_bytes(int head_dim) { return (size_t)2 * kStreamBlocks * 256 * (head_dim + 2) * sizeof(float); }
+
+bool stream_plan(const BatchMeta& m, int heads, int head_dim, StreamPlan* out) {
+  if (head_dim != 128) return false;
+  StreamPlan p{};
+  p.sc = make_sched(m, 256);
+  if (p.sc.n == 0) return false;
+  auto len = [&](int slot) { return m.joint_off[p.sc.req[slot] + 1] - m.joint_off[p.sc.req[slot]]; };
+  long steps = 0, units0 = 0;
+  int n0 = 0;
+  for (int i = 0; i < p.sc.n;) {
+    int j = i;
+    while (j < p.sc.n && len(j) == len(i)) ++j;
+    const long units = (long)heads * (p.sc.tile_off[j] - p.sc.tile_off[i]);
+    const int nt = (len(i) + kKeyTile - 1) / kKeyTile;
+    if (i == 0) {
+      units0 = units;
+      n0 = nt;
+    }
+    steps += units * nt;
+    p.st.slot0[p.st.n_groups++] = i;
+    p.st.slot0[p.st.n_groups] = j;
+    i = j;
+  }
+  if (steps >= (1L << 30)) return false;
+  const long rounds = units0 / kStreamBlocks;
+  p.main_units = (int)(rounds * kStreamBlocks);
+  p.st.skip = p.main_units;
+  p.st.steps = (int)(steps - (long)p.main_units * n0);
+  p.st.run = (p.st.steps + kStreamBlocks - 1) / kStreamBlocks;
+  const double shared = (double)rounds * (n0 + 4) + p.st.run + 28;
+  const long last = units0 % kStreamBlocks;  // 256-query tiles of the last round
+  double other = (1.07 + 8.0 / n0) * (double)steps / kStreamBlocks;
+  if (p.st.n_groups == 1 && 2 * last > kStreamBlocks) {  // where 256-query tiles would run
+    const double part = std::min(1.0, 0.35 + 0.75 * (double)last / kStreamBlocks);
+    other = (n0 + 4) * (rounds > 0 ? (double)rounds + part : 0.9 * part);
+  }
+  if (p.st.steps == 0 || shared > 0.98 * other) return false;
+  *out = p;
+  return true;
+}
+
 size_t split_bytes(const SplitPlan& p, int head_dim) {
   return p.pieces ? (size_t)p.tail_units * p.pieces * 128 * (head_dim + 2) * sizeof(float) : 0;
 }
@@ -742,7 +942,28 @@ bool wide_64(long units, long units8) {
 
 template <int HD>
 hipError_t launch_attn_hd(const AttnArgs& a, hipStream_t s) {
-  const SplitPlan sp = a.split_buf ? split_plan(a.meta, a.heads, HD) : SplitPlan{0, 0, 0};
+  if constexpr (HD == 128) {
+    StreamPlan p;
+    if (a.split_buf && a.split_bytes >= stream_bytes(HD) && stream_plan(a.meta, a.heads, HD, &p)) {
+      if (p.main_units) {
+        AttnSched main = p.sc;
+        main.n = p.st.slot0[1];
+        AttnArgs b = a;
+        b.unit0 = 0;
+        b.units = p.main_units;
+        b.kv_pieces = 1;
+        hipLaunchKernelGGL((attn_bf16_kernel<8, HD, 2, kKeyTile, 1>), dim3((unsigned)p.main_units), dim3(512), 0, s, b,
+                           main);
+      }
+      hipLaunchKernelGGL((attn_stream_kernel<HD, kKeyTile>), dim3(kStreamBlocks), dim3(512), 0, s, a, p.sc, p.st);
+      hipLaunchKernelGGL((attn_stream_merge_kernel<HD, kKeyTile>), dim3(kStreamBlocks - 1, 4), dim3(256), 0, s, a, p.sc,
+                         p.st);
+      return hipGetLastError();
+    }
+  }
+  const SplitPlan sp = a.split_buf && a.split_bytes >= split_bytes(split_plan(a.meta, a.heads, HD), HD)
+                           ? split_plan(a.meta, a.heads, HD)
+                           : SplitPlan{0, 0, 0};
   if (sp.pieces) {
     const AttnSched sc = make_sched(a.meta, 128);
     AttnArgs b = a;
@@ -788,6 +1009,11 @@ hipError_t launch_attention_bf16(const AttnArgs& a, hipStream_t s) {
 
 size_t attn_split_bytes(const BatchMeta& m, int heads, int head_dim) {
   return split_bytes(split_plan(m, heads, head_dim), head_dim);
+}
+
+size_t attn_scratch_bytes(const BatchMeta& m, int heads, int head_dim) {
+  StreamPlan p;
+  return stream_plan(m, heads, head_dim, &p) ? stream_bytes(head_dim) : attn_split_bytes(m, heads, head_dim);
 }
 
 hipError_t launch_attention_f32(const AttnArgs& a, hipStream_t s) {

@@ -175,11 +175,13 @@ struct AttnArgs {
   int qk_off[kMaxReq + 1];
   int vt_off[kMaxReq + 1];
   BatchMeta meta;
-  // Scratch for splitting the key range of a launch's last, partly filled
-  // round of query tiles (bf16, head dim 128): at least
-  // attn_split_bytes(meta, heads, head_dim) bytes, or null (never split; the
-  // output bits then do not depend on how many other tiles share the launch).
+  // Scratch of split_bytes bytes for sharing out the key tiles of a launch's
+  // last rounds (bf16, head dim 128), or null (never split; the output bits
+  // then do not depend on how many other tiles share the launch).  With at
+  // least attn_scratch_bytes() the launcher takes its best plan, with at least
+  // attn_split_bytes() the key split of a short last round.
   float* split_buf;
+  size_t split_bytes;
   // whether the order of a query's sums may depend on how many tiles the launch has
   int allow_split;
   // set by the launcher: this launch covers query-tile units
@@ -189,6 +191,8 @@ struct AttnArgs {
 };
 hipError_t launch_attention_bf16(const AttnArgs& a, hipStream_t s);
 // bytes of split_buf the bf16 launcher may use for this batch (0: it never splits)
+size_t attn_scratch_bytes(const BatchMeta& m, int heads, int head_dim);
+// bytes of split_buf of the key split alone
 size_t attn_split_bytes(const BatchMeta& m, int heads, int head_dim);
 hipError_t launch_attention_f32(const AttnArgs& a, hipStream_t s);
 

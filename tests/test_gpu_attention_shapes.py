@@ -69,3 +69,45 @@ def test_attention_key_groups(grids, n_txt, heads, d, gain):
         sl = slice(off, off + L)
         assert normwise_err(got[sl], O.attention(q64[sl], k64[sl], v[sl].astype(np.float64))) < BF16_TOL
         off += L
+
+
+@pytest.mark.parametrize("grids,n_txt,heads,shared", [
+    ([(92, 92)], [0], 24, True),                          # 34 tiles x 24 heads: 3 rounds and 48 tiles in 256 runs
+    ([(92, 92), (20, 25), (1, 1)], [7, 0, 0], 24, True),  # mixed lengths: whole short tiles inside runs
+    ([(128, 128)], [512], 6, True),                       # one round, runs shorter than a tile
+    ([(64, 64)], [512], 24, False),                       # whole rounds only
+])
+def test_attention_evenly_shared_keys(grids, n_txt, heads, shared):
+    """Sampled rows and heads against the oracle (the rows at both ends of every tile among them), the same
+    bits on a second call, and a workspace without the runs' parts."""
+    import torch
+    d, lens = 128, [gh * gw + nt for (gh, gw), nt in zip(grids, n_txt)]
+    T, Tp = sum(lens), sum((L + 63) // 64 * 64 for L in lens)
+    gen = torch.Generator(device="cuda").manual_seed(33)
+    q, k, v = (torch.randn((T, heads, d), generator=gen, device="cuda", dtype=torch.bfloat16) for _ in range(3))
+    b = dit.Batch([g[0] for g in grids], [g[1] for g in grids], n_txt)
+    wsb = dit.attention_workspace_size(b, heads, d, dit.DIT_BF16)
+    vt = (heads * d * Tp * 2 + 255) // 256 * 256
+    assert (wsb >= vt + 512 * 256 * (d + 2) * 4) == shared
+    outs = []
+    for n in (wsb, wsb, vt + (33 << 20)):
+        ws = torch.full((n,), 255, dtype=torch.uint8, device="cuda")  # stale parts are NaN
+        o = torch.full((T, heads, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+        dit.dit_attention(b, heads, d, dit.DIT_BF16, q, k, v, o, ws, n)
+        torch.cuda.synchronize()
+        outs.append(o)
+    assert torch.equal(outs[0], outs[1])
+    assert torch.isfinite(outs[0]).all()
+    # every element, against the plan without shared keys: two roundings of P to bf16 and one of O apart
+    diff = (outs[0].float() - outs[2].float()).norm() / outs[2].float().norm()
+    assert diff < 2 ** -7, diff
+    rng, off = np.random.default_rng(33), 0
+    for L in lens:
+        rows = np.unique(np.concatenate([np.arange(0, L, 256), np.arange(255, L, 256), [L - 1],
+                                         rng.integers(0, L, min(L, 40))]))
+        sl = slice(off, off + L)
+        for h in (0, heads // 2, heads - 1):
+            x = [t[sl, h:h + 1].float().cpu().numpy().astype(np.float64) for t in (q, k, v)]
+            ref = O.attention(*x, rows=rows)
+            assert normwise_err(outs[0][sl, h:h + 1].float().cpu().numpy()[rows], ref) < BF16_TOL
+        off += L
