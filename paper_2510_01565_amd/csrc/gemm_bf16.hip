@@ -112,26 +112,43 @@ __device__ __forceinline__ void epilogue_group(const EpiArgs& E, const RowEntry*
   if (n >= N || m >= M) return;
   const int v0 = E.mode == EPI_QKV ? 2 * E.hidden : N, v1 = E.mode == EPI_QKV ? 3 * E.hidden : N;  // V columns
   if (n < v1 && n + W > v0) {
-    // a lane takes one column and 16 consecutive rows, which (when they are 16
-    // consecutive, 16-aligned padded positions of one request) land in one
-    // aligned 16-key group of V^T: two 16-byte stores
+    // A lane takes one column of the group.  Rows at consecutive positions of
+    // one request are consecutive keys of V^T: two 16-key groups (four 16-byte
+    // stores) when they start on one, else quads of keys (8-byte stores) between
+    // up to three single keys at either end.  Image counts that are not a
+    // multiple of 16 leave every later row unaligned; with a 2-byte store per
+    // key a QKV launch of 8056 x 21504 x 3072 (67 x 116 image) took 896 us between
+    // events, now 826, and 24 of 3414 x 4608 x 1536 93 -> 68 us each.
     const int hn = n + lane - v0, h = hn / E.head_dim, dd = hn - h * E.head_dim;
     if (lane < W && n + lane >= v0 && n + lane < v1 && n + lane < N) {
       bf16_t* vt = (bf16_t*)E.vt + ((long)h * E.head_dim + dd) * E.vt_ld;
+      const int p0 = rows[0].pos;
+      if (m + 31 < M && rows[31].pos == p0 + 31) {
+        if ((p0 & 15) == 0) {
 #pragma unroll
-      for (int r16 = 0; r16 < 32; r16 += 16) {
-        if (m + r16 >= M) break;
-        const RowEntry r0 = rows[r16];
-        if (m + r16 + 15 < M && (r0.pos & 15) == 0 && rows[r16 + 15].pos == r0.pos + 15) {
-          // slot s of the group holds key vt_slot(s): swap the middle quads
-          float w[16];
+          for (int r16 = 0; r16 < 32; r16 += 16) {
+            // slot s of a group holds key vt_slot(s): swap the middle quads
+            float w[16];
 #pragma unroll
-          for (int q = 0; q < 16; ++q) w[q] = stg[(r16 + vt_slot(q)) * SP + lane];
-          store16<bf16_t>(vt + r0.pos, w);
+            for (int q = 0; q < 16; ++q) w[q] = stg[(r16 + vt_slot(q)) * SP + lane];
+            store16<bf16_t>(vt + p0 + r16, w);
+          }
         } else {
-          for (int q = 0; q < 16; ++q)
-            if (m + r16 + q < M) vt[vt_slot(rows[r16 + q].pos)] = f2bf(stg[(r16 + q) * SP + lane]);
+          const int a = -p0 & 3;  // rows ahead of the first whole quad
+          const float* col = stg + a * SP + lane;
+          for (int q = 0; q < a; ++q) vt[vt_slot(p0 + q)] = f2bf(stg[q * SP + lane]);
+#pragma unroll
+          for (int t = 0; t < 8; ++t) {
+            if (t == 7 && a > 0) break;
+            uint2 w;
+            w.x = pack_bf16x2(col[(4 * t) * SP], col[(4 * t + 1) * SP]);
+            w.y = pack_bf16x2(col[(4 * t + 2) * SP], col[(4 * t + 3) * SP]);
+            *(uint2*)(vt + vt_slot(p0 + a + 4 * t)) = w;
+          }
+          for (int q = 28 + a; a > 0 && q < 32; ++q) vt[vt_slot(p0 + q)] = f2bf(stg[q * SP + lane]);
         }
+      } else {
+        for (int q = 0; q < 32 && m + q < M; ++q) vt[vt_slot(rows[q].pos)] = f2bf(stg[q * SP + lane]);
       }
     }
     if (n >= v0 && n + W <= v1) return;

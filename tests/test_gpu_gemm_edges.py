@@ -68,3 +68,18 @@ def test_linear_f32_tiles(M, N, K):
     torch.cuda.synchronize()
     got = y[1:].cpu().numpy().reshape(M, N)
     assert np.abs(got - ref).max() <= 2 ** -23 * np.sqrt(K) * 0.02 * np.sqrt(K) * 4 + 1e-9
+
+
+def test_vt_rows_at_every_alignment():
+    """Requests whose rows start at positions 0 .. 3 modulo 4 and elsewhere in 16-key groups, in runs longer
+    and shorter than an epilogue group of 32 rows, as image and as text rows (both kinds of block)."""
+    m = workloads.ModelShape(hidden=192, heads=3, head_dim=64, mlp_ratio=2, n_double=1, n_single=1,
+                             in_channels=64, text_dim=64)
+    cfg, shapes, params = host_params(m, 14)
+    grids = [(1, 1), (5, 7), (6, 11), (3, 1), (8, 9), (7, 19), (2, 47), (16, 16)]
+    n_txt = [65, 0, 70, 33, 40, 67, 98, 3]
+    ts = [0.1 * (i + 1) for i in range(len(grids))]
+    lat, txt = request_inputs(m, grids, n_txt, 14)
+    vel, _, _ = _run_step(m, params, shapes, cfg, grids, n_txt, ts, lat, txt)
+    ref = np.concatenate(_oracle_step(m, params, grids, n_txt, ts, lat, txt))
+    assert normwise_err(vel.float().cpu().numpy(), ref) < BF16_TOL
