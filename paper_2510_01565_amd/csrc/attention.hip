@@ -928,7 +928,10 @@ size_t split_bytes(const SplitPlan& p, int head_dim) {
 // 16 717 tokens and 3 - 24 heads: a full round costs 1.6 (768 units) and 1.95
 // (512 blocks), and the last round 0.4 / 0.87 / 1.36 for up to 1 / 2 / 3
 // 128-query blocks per CU and 0.9 / 1.76 for up to 1 / 2 256-query blocks.  Up
-// to 768 units the 128-query blocks are never slower.  Against one 256-query
+// to 768 units the 128-query blocks are never slower.  In a batch of mixed
+// lengths the last round holds the shortest tiles and costs less than this, so
+// 256-query blocks are taken there only if they all fit at once (2097 + 1970
+// tokens, 24 heads: 792 units in two rounds or 408 blocks in one).  Against one 256-query
 // block per CU at every size: 210 units 75 -> 53 us, 528 101 -> 76, 840
 // 154 -> 143, 1584 566 -> 481, 3144 1737 -> 1735; a packed batch of 589, 1357 and
 // 4429 tokens (12 heads) 148 -> 110.
@@ -990,7 +993,9 @@ hipError_t launch_attn_hd(const AttnArgs& a, hipStream_t s) {
   const AttnSched sc8 = make_sched(a.meta, 8 * 32);
   const long units8 = (long)sc8.tile_off[sc8.n] * a.heads;
   constexpr long kSlots8 = 256;  // 256-query blocks resident per GPU at head dim 128 (one per CU)
-  const bool wide = equal && (HD == 128 ? 2 * (units8 % kSlots8) > kSlots8 : wide_64(units, units8));
+  const long last8 = units8 % kSlots8;
+  const bool wide = HD == 128 ? equal && (last8 == 0 || 2 * last8 > kSlots8)
+                              : wide_64(units, units8) && (equal || units8 <= 512);
   // Two key groups per block where every block has a CU to itself and at least
   // 20 key tiles: 168 units x 28 tiles 62.6 -> 52.2 us at head dim 128 and 42.6
   // -> 36.9 at 64, 240 x 40 88.7 -> 81.4 and 57.5 -> 51.6, 240 x 20 32.2 -> 31.1

@@ -1044,7 +1044,8 @@ struct TileModel {
 // 256 busy CUs long enough for power to set the clock, and there the 256x128
 // and 128x256 tiles, which move 1.5 times the operand bytes per FLOP, fall
 // further behind than their one-round rates say (7622 x 3072 x 12288 inside a
-// step: 540 us in 3 rounds of 256x128, 500 us in 2 of 256x256): kSustainedLoss.
+// step: 540 us in 3 rounds of 256x128, 500 us in 2 of 256x256; 8056 x 3072 x
+// 15360: 55 us more with the narrower tile): kSustainedLoss.
 // With both, one single block at 1024 px 1064 -> 1051 us (linear2 on 256x256
 // instead of 288x192), a packed 7622-row double block 1991 -> 1948 us, the
 // 57-block 1024 px step 63.4 -> 63.0 ms, other sizes unchanged.
@@ -1059,7 +1060,7 @@ constexpr TileModel kTileModels[] = {
     {CFG_128x128, 128, 128, 5.07, 4.1},
     {CFG_288x192, 288, 192, 6.31, 8.0},
 };
-constexpr double kSustainedLoss = 1.07;
+constexpr double kSustainedLoss = 1.1;
 // Split K: the merge adds, on the critical path, the write of a piece's
 // partial sums and the last piece's read of the others' (fp32, bm x bn per
 // piece) plus the arrival handshake.  A split is taken only when the model
