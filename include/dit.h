@@ -222,13 +222,12 @@ dit_status euler_update(const dit_batch* batch, int channels, int dtype, void* l
  * accumulation, P rounded to bf16 for P V), 64 for DIT_F32 (all fp32);
  * anything else returns DIT_ERR_UNSUPPORTED before any launch.
  * ws: at least dit_attention_workspace_size() bytes: V^T, plus for DIT_BF16
- * at head_dim 128 the fp32 partial results of query tiles whose keys are shared
- * out over several blocks, merged in a fixed order (bitwise repeatable).  Two
- * plans use them: the key split of a short last round of 128-query tiles (two
- * per CU, at most a quarter full after two or more full rounds, requests of
- * one length; up to 33 MiB), and the even sharing of all key tiles past the
- * last full round of 256-query tiles, where it is the faster one (65 MiB).
- * A workspace that holds V^T and the former's results only is accepted too.
+ * at head_dim 128, when the last round of 128-query tiles (two per CU) is at
+ * most a quarter full after two or more full rounds and every request has one
+ * length, the fp32 partial results of those tiles' key ranges (up to 33 MiB),
+ * merged in a fixed order (bitwise repeatable).  With a workspace of 66 MiB
+ * more than V^T, DIT_BF16 at head_dim 128 may instead share out all key tiles
+ * past the last full round of 256-query tiles evenly, where that is faster.
  */
 dit_status dit_attention_workspace_size(const dit_batch* batch, int heads, int head_dim, int dtype,
                                         size_t* bytes);

@@ -1016,11 +1016,6 @@ size_t attn_split_bytes(const BatchMeta& m, int heads, int head_dim) {
   return split_bytes(split_plan(m, heads, head_dim), head_dim);
 }
 
-size_t attn_scratch_bytes(const BatchMeta& m, int heads, int head_dim) {
-  StreamPlan p;
-  return stream_plan(m, heads, head_dim, &p) ? stream_bytes(head_dim) : attn_split_bytes(m, heads, head_dim);
-}
-
 hipError_t launch_attention_f32(const AttnArgs& a, hipStream_t s) {
   if (a.head_dim != FD) return hipErrorInvalidValue;
   const AttnSched sc = make_sched(a.meta, FQ);

@@ -911,7 +911,7 @@ dit_status dit_attention_workspace_size(const dit_batch* batch, int heads, int h
   if (dtype != DIT_F32 && dtype != DIT_BF16) return fail(DIT_ERR_INVALID_ARG, "dtype %d", dtype);
   const BatchMeta m = make_meta(batch);
   *bytes = align256((size_t)heads * head_dim * m.pad_off[m.n_req] * elem_size(dtype));
-  if (dtype == DIT_BF16) *bytes += align256(attn_scratch_bytes(m, heads, head_dim));
+  if (dtype == DIT_BF16) *bytes += align256(attn_split_bytes(m, heads, head_dim));
   return DIT_OK;
 }
 
@@ -928,11 +928,10 @@ dit_status dit_attention(const dit_batch* batch, int heads, int head_dim, int dt
   if (!aligned16(q) || !aligned16(k) || !aligned16(v) || !aligned16(o))
     return fail(DIT_ERR_INVALID_ARG, "q / k / v / o must be 16-byte aligned");
   const BatchMeta m = make_meta(batch);
-  // V^T, and the key split's scratch where it applies; a workspace of
-  // dit_attention_workspace_size() also holds the evenly shared runs' parts
-  const size_t vt_bytes = align256((size_t)heads * head_dim * m.pad_off[m.n_req] * elem_size(dtype));
-  const size_t need = vt_bytes + (dtype == DIT_BF16 ? align256(attn_split_bytes(m, heads, head_dim)) : 0);
+  size_t need = 0;
+  dit_attention_workspace_size(batch, heads, head_dim, dtype, &need);
   if ((st = check_ws(ws, ws_bytes, need))) return st;
+  const size_t vt_bytes = align256((size_t)heads * head_dim * m.pad_off[m.n_req] * elem_size(dtype));
   hipStream_t s = (hipStream_t)stream;
   HIP_TRY(timed(s, "v_transpose", 0.0, 2.0 * m.T * heads * head_dim * elem_size(dtype),
                 [&] { return launch_v_transpose(dtype, v, m, heads, head_dim, ws, s); }));

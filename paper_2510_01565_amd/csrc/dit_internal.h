@@ -177,9 +177,8 @@ struct AttnArgs {
   BatchMeta meta;
   // Scratch of split_bytes bytes for sharing out the key tiles of a launch's
   // last rounds (bf16, head dim 128), or null (never split; the output bits
-  // then do not depend on how many other tiles share the launch).  With at
-  // least attn_scratch_bytes() the launcher takes its best plan, with at least
-  // attn_split_bytes() the key split of a short last round.
+  // then do not depend on how many other tiles share the launch).  The key
+  // split of a short last round needs attn_split_bytes(), even sharing 65 MiB.
   float* split_buf;
   size_t split_bytes;
   // whether the order of a query's sums may depend on how many tiles the launch has
@@ -190,9 +189,7 @@ struct AttnArgs {
   int unit0, units, kv_pieces;
 };
 hipError_t launch_attention_bf16(const AttnArgs& a, hipStream_t s);
-// bytes of split_buf the bf16 launcher may use for this batch (0: it never splits)
-size_t attn_scratch_bytes(const BatchMeta& m, int heads, int head_dim);
-// bytes of split_buf of the key split alone
+// bytes of split_buf for the key split of a short last round (0: it does not apply)
 size_t attn_split_bytes(const BatchMeta& m, int heads, int head_dim);
 hipError_t launch_attention_f32(const AttnArgs& a, hipStream_t s);
 
