@@ -3,18 +3,25 @@
 // bf16 kernel.  Used by fp32 models.
 //
 // The fp32 models are small: their launches hold a few hundred rows and wait
-// for memory, not for the matrix cores (2 us of MFMAs in the old kernel's
-// 33 us).  So operands go straight from memory to registers, 16 bytes per
-// lane, four to eight 16-wide K chunks in flight per wave, with no LDS round
-// trip or barrier before the end.  A lane's four consecutive K values feed four
-// MFMAs (K is summed in the order 0 4 8 12, 1 5 9 13, ... inside a chunk, on
-// both operands alike).  Every wave owns 32 x 32 outputs; a block's four waves
-// share one such tile and split its K range when 64 x 64 tiles would not give
-// each of the 256 CUs a block, and take a quarter each of a 64 x 64 tile
-// otherwise.  The partial sums meet in LDS and are added in wave order.
+// for memory, not for the matrix cores.  So operands go straight from memory to
+// registers, 16 bytes per lane, with no LDS round trip or barrier before the
+// end.  A lane's four consecutive K values feed four MFMAs (K is summed in the
+// order 0 4 8 12, 1 5 9 13, ... inside a chunk, on both operands alike).  A
+// block owns 32 x 32 outputs; its four waves split the K range, and the partial
+// sums meet in LDS and are added in wave order.  That many small blocks also
+// win where there is work for 64 x 64 tiles without a split (M 1100, N 1024,
+// K 1024: 42 against 63 us; M 4096, N 3072, K 1024: 366 against 391 us).
 // M 288, N 16 - 1536, K 16 - 1536 (the six launches of the small model's step
-// at 256 px): 14.5 us per launch between events, launch included, against 43 us
-// for 64 x 64 tiles on the vector ALUs; the step 367 -> 106 us with attention.
+// at 256 px): 12.1 us per launch between events, launch included, against 43 us
+// for 64 x 64 tiles on the vector ALUs.
+//
+// G is the number of 16-wide K chunks in each of a wave's two register buffers.
+// With a block or more for each CU, waves hide each other's latency and G = 1
+// wins (5 waves per SIMD, with G = 4 it is 3): M 288, N 1152, K 384 G = 1, 2, 4:
+// 9.1, 9.9, 12.7 us.  Below that a wave has to hide it alone: M 288, N 384,
+// K 1536 (108 blocks) 17.1, 16.0, 16.9 us; M 7, N 1024, K 4096 (32 blocks, 64
+// chunks per wave) 33.3, 30.2, 28.9 us.
+// G changes no order of sums, so a row's result does not depend on the batch.
 #include "device_common.h"
 
 namespace dit {
@@ -23,7 +30,6 @@ namespace {
 
 constexpr int WT = 32;       // a wave's tile
 constexpr int SP = WT + 4;   // LDS row pitch of a staged tile
-constexpr int G = 4;         // 16-wide K chunks loaded together
 
 // Four consecutive outputs n .. n+3 (n a multiple of 4) of row m, bias added.
 __device__ __forceinline__ void store4(float* dst, int left, float4 y) {
@@ -85,15 +91,12 @@ __device__ __forceinline__ void epilogue4(const GemmProblem& P, const EpiArgs& E
   }
 }
 
-// KS waves of a block split the K range of one 32 x 32 tile (4), or none does
-// and the four waves form a 64 x 64 tile (1)
-template <int KS>
+template <int G>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(const GemmProblem P) {
-  constexpr int TB = KS == 4 ? WT : 2 * WT;  // block tile side
   __shared__ float red[4][WT * SP];
 
-  const int tiles_n = (P.N + TB - 1) / TB;
-  const int tm0 = (P.g[0].M + TB - 1) / TB;
+  const int tiles_n = (P.N + WT - 1) / WT;
+  const int tm0 = (P.g[0].M + WT - 1) / WT;
   int id = blockIdx.x;
   int gi = 0;
   if (id >= tm0 * tiles_n) {
@@ -108,10 +111,13 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const GemmProblem P) {
   const int K = gi ? P.g[1].K : P.g[0].K;
   const int N = P.N;
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int part = KS == 4 ? wave : 0;
-  const int m0 = id / tiles_n * TB + (KS == 4 ? 0 : (wave >> 1) * WT);
-  const int n0 = id % tiles_n * TB + (KS == 4 ? 0 : (wave & 1) * WT);
+  const int tid = threadIdx.x, lane = tid & 63;
+  // with a scalar wave number the loop's guards are branches, otherwise lane
+  // masks.  Branches win where a wave hides its own latency (M 7, N 1024,
+  // K 4096: 28.2 against 28.9 us), masks with G = 1 (M 1100, N 1024, K 1024:
+  // 41.9 against 43.9 us; M 8192, N 9216, K 1024: 2209 against 2418 us)
+  const int wave = G == 1 ? tid >> 6 : __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int m0 = id / tiles_n * WT, n0 = id % tiles_n * WT;
 
   // lane: row lane % 16 of a 16-row fragment, K values 4 (lane / 16) .. + 3 of
   // a chunk.  Rows past the edge re-read the last one (their products reach
@@ -125,7 +131,7 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const GemmProblem P) {
     pb[i] = W + (long)min(n0 + i * 16 + (lane & 15), N - 1) * ldw;
   }
   const int chunks = (K + 15) / 16;
-  const int c0 = part * chunks / KS, c1 = (part + 1) * chunks / KS;
+  const int c0 = wave * chunks / 4, c1 = (wave + 1) * chunks / 4;
   f32x4_t acc[2][2] = {};
   float4 fa[2][G][2], fb[2][G][2];
   auto load = [&](auto bufc, int c) __attribute__((always_inline)) {
@@ -162,10 +168,10 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const GemmProblem P) {
   using B1 = std::integral_constant<int, 1>;
   load(B0{}, c0);
   for (int c = c0; c < c1; c += 2 * G) {
-    load(B1{}, c + G);
+    if (c + G < c1) load(B1{}, c + G);
     multiply(B0{}, c);
-    load(B0{}, c + 2 * G);
-    multiply(B1{}, c + G);
+    if (c + 2 * G < c1) load(B0{}, c + 2 * G);
+    if (c + G < c1) multiply(B1{}, c + G);
   }
 
   // stage: column lane % 16 of a 16 x 16 block, rows 4 (lane / 16) .. + 3
@@ -180,52 +186,50 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const GemmProblem P) {
 
   const EpiArgs E = gi ? P.g[1].epi : P.g[0].epi;
   const float* bias = (const float*)E.bias;
-  // pieces of 4 columns, consecutive lanes along a row; for V columns along
+  // a thread writes 4 columns, consecutive lanes along a row; for V columns along
   // the rows, which are consecutive in V^T
   const bool vcols = E.mode == EPI_QKV && n0 >= 2 * E.hidden && n0 < E.n_qkv;
-#pragma unroll 1
-  for (int p = KS == 4 ? tid : lane; p < WT * WT / 4; p += KS == 4 ? 256 : 64) {
-    const int r = vcols ? p & 31 : p >> 3, c = vcols ? (p >> 5) * 4 : (p & 7) * 4;
-    const int m = m0 + r, n = n0 + c;
-    if (m >= M || n >= N) continue;
-    float4 y = *(const float4*)&red[KS == 4 ? 0 : wave][r * SP + c];
-    if constexpr (KS == 4) {
+  const int r = vcols ? tid & 31 : tid >> 3, c = vcols ? (tid >> 5) * 4 : (tid & 7) * 4;
+  const int m = m0 + r, n = n0 + c;
+  if (m >= M || n >= N) return;
+  float4 y = *(const float4*)&red[0][r * SP + c];
 #pragma unroll
-      for (int w = 1; w < 4; ++w) {
-        const float4 t = *(const float4*)&red[w][r * SP + c];
-        y.x += t.x;
-        y.y += t.y;
-        y.z += t.z;
-        y.w += t.w;
-      }
-    }
-    if (bias) {
-      y.x += bias[n];
-      if (n + 1 < N) y.y += bias[n + 1];
-      if (n + 2 < N) y.z += bias[n + 2];
-      if (n + 3 < N) y.w += bias[n + 3];
-    }
-    epilogue4(P, E, m, n, y);
+  for (int w = 1; w < 4; ++w) {
+    const float4 t = *(const float4*)&red[w][r * SP + c];
+    y.x += t.x;
+    y.y += t.y;
+    y.z += t.z;
+    y.w += t.w;
   }
-}
-
-template <int KS>
-hipError_t launch(const GemmProblem& p, hipStream_t s) {
-  constexpr int TB = KS == 4 ? WT : 2 * WT;
-  const long tn = (p.N + TB - 1) / TB;
-  long tiles = 0;
-  for (int g = 0; g < p.n_groups; ++g) tiles += (long)((p.g[g].M + TB - 1) / TB) * tn;
-  if (tiles == 0) return hipSuccess;
-  hipLaunchKernelGGL(gemm_f32_kernel<KS>, dim3((unsigned)tiles), dim3(256), 0, s, p);
-  return hipGetLastError();
+  if (bias) {
+    y.x += bias[n];
+    if (n + 1 < N) y.y += bias[n + 1];
+    if (n + 2 < N) y.z += bias[n + 2];
+    if (n + 3 < N) y.w += bias[n + 3];
+  }
+  epilogue4(P, E, m, n, y);
 }
 
 }  // namespace
 
 hipError_t launch_gemm_f32(const GemmProblem& p, hipStream_t s) {
-  long tiles64 = 0;
-  for (int g = 0; g < p.n_groups; ++g) tiles64 += (long)((p.g[g].M + 63) / 64) * ((p.N + 63) / 64);
-  return tiles64 < 256 ? launch<4>(p, s) : launch<1>(p, s);
+  long tiles = 0;
+  int kmax = 0;
+  for (int g = 0; g < p.n_groups; ++g) {
+    tiles += (long)((p.g[g].M + WT - 1) / WT) * ((p.N + WT - 1) / WT);
+    kmax = p.g[g].K > kmax ? p.g[g].K : kmax;
+  }
+  if (tiles == 0) return hipSuccess;
+  const dim3 grid((unsigned)tiles), block(256);
+  // K 2048: 32 chunks per wave.  Below a block per CU the two buffers of 2
+  // chunks do for K up to there, longer K want the 8 chunks in flight
+  if (tiles >= 256)
+    hipLaunchKernelGGL(gemm_f32_kernel<1>, grid, block, 0, s, p);
+  else if (kmax <= 2048)
+    hipLaunchKernelGGL(gemm_f32_kernel<2>, grid, block, 0, s, p);
+  else
+    hipLaunchKernelGGL(gemm_f32_kernel<4>, grid, block, 0, s, p);
+  return hipGetLastError();
 }
 
 }  // namespace dit

@@ -53,11 +53,12 @@ def test_step_width_not_a_multiple_of_the_wave_tile():
 
 
 @pytest.mark.parametrize("M,N,K", [
-    (1, 1, 8), (33, 31, 24), (32, 32, 16), (65, 130, 72),   # K split over a block's waves: fewer chunks than waves, odd tails
-    (1024, 1024, 40), (1025, 1030, 264),                    # 256 and more 64x64 tiles: a wave each
+    (1, 1, 8), (33, 31, 24), (32, 32, 16), (65, 130, 72),   # fewer chunks than waves, odd tails
+    (40, 70, 2048), (100, 33, 2056), (511, 480, 40),        # below 256 blocks: the last K of 2 chunks per buffer, more
+    (512, 512, 8), (1024, 1024, 40), (1025, 1030, 264),     # 256 blocks and more: 1 chunk per buffer
 ])
 def test_linear_f32_tiles(M, N, K):
-    """fp32 GEMM at the edges of its two tilings, without bias and with an output that is not 16-byte aligned;
+    """fp32 GEMM at the edges of its tiles and buffer depths, without bias and with an output that is not 16-byte aligned;
     K products of N(0, 1) x N(0, 0.02^2) summed in fp32: error below sqrt(K) 2^-23 of the sums' scale."""
     import torch
     x = synth.normal(13, "x", (M, K))
