@@ -607,20 +607,21 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const AttnArgs a, const
 // ----------------------------------------------------------------------------
 // fp32 attention (head_dim 64) for fp32 models, on the fp32 matrix cores
 // (v_mfma_f32_16x16x4_f32: fp32 products and sums).  A block owns 16 queries of
-// a head; its four waves take the 16-key tiles in turn, each with its own
-// running max, sum and O, and the four results are merged at the end in wave
-// order.  A tile's scores are S^T = K Q^T, so a lane holds four keys of one
-// query; as in the bf16 kernel the probabilities feed O^T = V^T P^T from
-// registers: MFMA step r of a tile takes key 4 (lane / 16) + r from every lane
-// quarter, and V^T's 16-byte pieces hold the same keys (its middle quads are
-// swapped in memory).  K and V^T go straight from memory to registers, the
-// next tile's loads under this tile's MFMAs.  The small model's launches
-// (288 keys, 6 heads) are bound by latency: 108 blocks with 5 tiles per wave
-// instead of 30 blocks with 5 tiles of 64;
-// 13.4 us between events, launch included, against 98 us for four lanes per
-// query on the vector ALUs.  exp2 of a
-// log2(e)-scaled argument adds one rounding of the argument (about 2e-6
-// relative at the scores met).
+// a head; its four waves share out the 16-key tiles, each with its own running
+// max, sum and O, and the four results are merged at the end in wave order.
+// A tile's scores are S^T = K Q^T, so a lane holds four keys of one query; as in
+// the bf16 kernel the probabilities feed O^T = V^T P^T from registers: MFMA
+// step r of a tile takes key 4 (lane / 16) + r from every lane quarter, and
+// V^T's 16-byte pieces hold the same keys (its middle quads are swapped in
+// memory).  K and V^T go straight from memory to registers; the next tile's K
+// replaces this one's once the scores are done, its V^T once O is.  The small
+// model's launches (288 keys, 6 heads) are bound by latency: 108 blocks with 5
+// tiles per wave; 13 us between events, launch included, against 98 us for four
+// lanes per query on the vector ALUs.  Two or three tiles per step, or whole
+// tiles loaded one step ahead into a second set of registers, are 0-4% slower
+// over the small model's whole step (288 keys: 92.4, 93.0, 93.5 against 91.7 us;
+// 2336 keys: 333, 348, 341 against 328 us).  exp2 of a log2(e)-scaled argument
+// adds one rounding of the argument (about 2e-6 relative at the scores met).
 constexpr int FD = 64;
 constexpr int FQ = 16;
 
@@ -650,15 +651,16 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(const AttnArgs a, const A
   // V^T row 16 c + lr, the four slots that hold keys 4 kq .. + 3 of a tile
   const int vq = vt_slot(kq * 4);
   const int nt = (L + 15) / 16;
-  float4 kf[2][4], vf[2][4];
-  auto load = [&](auto bufc, int j) __attribute__((always_inline)) {
-    constexpr int buf = decltype(bufc)::value;
-    const int jj = min(j, nt - 1);  // past the last tile: loaded again, not used
+  const int t0 = wave * nt / 4, t1 = (wave + 1) * nt / 4;  // the wave's tiles
+  float4 kf[4], vf[4];
+  auto load_k = [&](int j) __attribute__((always_inline)) {
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      kf[buf][c] = *(const float4*)(Kg + (long)min(jj * 16 + lr, L - 1) * a.k_tok + c * 16 + kq * 4);
-      vf[buf][c] = *(const float4*)(Vg + (long)(c * 16 + lr) * a.vt_d + jj * 16 + vq);
-    }
+    for (int c = 0; c < 4; ++c)
+      kf[c] = *(const float4*)(Kg + (long)min(j * 16 + lr, L - 1) * a.k_tok + c * 16 + kq * 4);
+  };
+  auto load_v = [&](int j) __attribute__((always_inline)) {
+#pragma unroll
+    for (int c = 0; c < 4; ++c) vf[c] = *(const float4*)(Vg + (long)(c * 16 + lr) * a.vt_d + j * 16 + vq);
   };
   auto at = [](const float4& v, auto ec) __attribute__((always_inline)) {
     constexpr int e = decltype(ec)::value;
@@ -667,16 +669,20 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(const AttnArgs a, const A
   const float sl2 = a.scale * kLog2e;
   float m = -INFINITY, l = 0.f;  // m: of the query, in the log2 domain; l: of this lane's keys
   f32x4_t o[4] = {};             // O^T rows 16 c + 4 kq .. + 3 of query lr
-  auto tile = [&](auto bufc, int j) __attribute__((always_inline)) {
-    constexpr int buf = decltype(bufc)::value;
+  if (t0 < t1) {
+    load_k(t0);
+    load_v(t0);
+  }
+  for (int j = t0; j < t1; ++j) {
     // two chains of MFMAs: each result waits for the one before it
     f32x4_t s0 = {}, s1 = {};
 #pragma unroll
     for (int c = 0; c < 4; c += 2)
       static_for<4>([&](auto ec) {
-        s0 = __builtin_amdgcn_mfma_f32_16x16x4f32(at(kf[buf][c], ec), at(q[c], ec), s0, 0, 0, 0);
-        s1 = __builtin_amdgcn_mfma_f32_16x16x4f32(at(kf[buf][c + 1], ec), at(q[c + 1], ec), s1, 0, 0, 0);
+        s0 = __builtin_amdgcn_mfma_f32_16x16x4f32(at(kf[c], ec), at(q[c], ec), s0, 0, 0, 0);
+        s1 = __builtin_amdgcn_mfma_f32_16x16x4f32(at(kf[c + 1], ec), at(q[c + 1], ec), s1, 0, 0, 0);
       });
+    if (j + 1 < t1) load_k(j + 1);
     float s[4], mx = m;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -700,17 +706,9 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(const AttnArgs a, const A
     static_for<4>([&](auto ec) {
 #pragma unroll
       for (int c = 0; c < 4; ++c)
-        o[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(at(vf[buf][c], ec), s[decltype(ec)::value], o[c], 0, 0, 0);
+        o[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(at(vf[c], ec), s[decltype(ec)::value], o[c], 0, 0, 0);
     });
-  };
-  using B0 = std::integral_constant<int, 0>;
-  using B1 = std::integral_constant<int, 1>;
-  load(B0{}, wave);
-  for (int j = wave; j < nt; j += 8) {
-    load(B1{}, j + 4);
-    tile(B0{}, j);
-    load(B0{}, j + 8);
-    if (j + 4 < nt) tile(B1{}, j + 4);
+    if (j + 1 < t1) load_v(j + 1);
   }
   l += __shfl_xor(l, 16, 64);
   l += __shfl_xor(l, 32, 64);
@@ -719,7 +717,7 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(const AttnArgs a, const A
   for (int c = 0; c < 4; ++c) *(float4*)&osh[wave][lr][c * 16 + kq * 4] = make_float4(o[c][0], o[c][1], o[c][2], o[c][3]);
   __syncthreads();
   // 16 lanes per query, 4 dims each.  A wave without a tile has max -inf and
-  // weighs nothing; wave 0 always has one.
+  // weighs nothing; wave 3 always has one.
   const int ql = tid >> 4, dd = (tid & 15) * 4, qrow = q0 + ql;
   if (qrow >= L) return;
   float mm = ml[0][ql].x;
