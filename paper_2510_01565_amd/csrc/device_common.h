@@ -68,30 +68,6 @@ __device__ __forceinline__ float gelu_tanh(float x) {
 
 __device__ __forceinline__ float silu(float x) { return x / (1.0f + __expf(-x)); }
 
-// Per-row facts an epilogue needs, computed once per output tile row.
-struct RowEntry {
-  int req;  // request index
-  int pos;  // position in the padded joint layout of Q / K / V^T
-  int gi;   // grid row of an image token, -1 for text
-  int gj;   // grid column of an image token
-};
-
-__device__ __forceinline__ RowEntry make_row_entry(const BatchMeta& meta, int R) {
-  const RowInfo ri = row_info(meta, R);
-  RowEntry e;
-  e.req = ri.req;
-  e.pos = padded_pos(meta, ri);
-  if (ri.is_img) {
-    const int gw = meta.grid_w[ri.req];
-    e.gi = ri.local / gw;
-    e.gj = ri.local - e.gi * gw;
-  } else {
-    e.gi = -1;
-    e.gj = 0;
-  }
-  return e;
-}
-
 // One output element of a GEMM epilogue.  `y` already includes the bias;
 // `y_pair` is the value of the partner column n ^ 1 (RoPE pairs), bias included.
 template <typename T>

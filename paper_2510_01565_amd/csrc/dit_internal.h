@@ -80,6 +80,39 @@ __host__ __device__ inline int padded_to_row(const BatchMeta& m, int r, int q) {
 // which one 32x32 score fragment holds them; an involution.
 __host__ __device__ inline int vt_slot(int pos) { return (pos & ~12) | ((pos & 4) << 1) | ((pos & 8) >> 1); }
 
+// Per-row facts an epilogue needs, computed once per output tile row.
+struct RowEntry {
+  int req;  // request index
+  int pos;  // position in the padded joint layout of Q / K / V^T
+  int gi;   // grid row of an image token, -1 for text
+  int gj;   // grid column of an image token
+};
+
+__host__ __device__ inline RowEntry make_row_entry(const BatchMeta& meta, int R) {
+  const RowInfo ri = row_info(meta, R);
+  RowEntry e;
+  e.req = ri.req;
+  e.pos = padded_pos(meta, ri);
+  if (ri.is_img) {
+    const int gw = meta.grid_w[ri.req];
+    e.gi = ri.local / gw;
+    e.gj = ri.local - e.gi * gw;
+  } else {
+    e.gi = -1;
+    e.gj = 0;
+  }
+  return e;
+}
+
+// Whether n stream-major rows, the first and the last of which are given, are n
+// consecutive tokens of one request.  Positions rise along the text rows and
+// along the image rows, but fall where one kind ends and the other begins and
+// jump by a request's padding, so the distance of the ends alone says it only
+// inside one kind.
+__host__ __device__ inline bool rows_consecutive(const RowEntry& first, const RowEntry& last, int n) {
+  return last.pos - first.pos == n - 1 && last.req == first.req && (last.gi < 0) == (first.gi < 0);
+}
+
 
 // ----------------------------------------------------------------------------
 // GEMM epilogues: Y = A W^T + bias, then one of

@@ -123,7 +123,7 @@ __device__ __forceinline__ void epilogue_group(const EpiArgs& E, const RowEntry*
     if (lane < W && n + lane >= v0 && n + lane < v1 && n + lane < N) {
       bf16_t* vt = (bf16_t*)E.vt + ((long)h * E.head_dim + dd) * E.vt_ld;
       const int p0 = rows[0].pos;
-      if (m + 31 < M && rows[31].pos == p0 + 31) {
+      if (m + 31 < M && rows_consecutive(rows[0], rows[31], 32)) {
         if ((p0 & 15) == 0) {
 #pragma unroll
           for (int r16 = 0; r16 < 32; r16 += 16) {

@@ -5,7 +5,8 @@ import numpy as np
 import pytest
 
 from paper_2510_01565_amd import dit, synth, workloads
-from harness import BF16_TOL, F32_TOL, host_params, normwise_err, request_inputs, to_dev
+from harness import (BF16_TOL, F32_TOL, host_params, normwise_err, request_inputs, to_dev, upload_params,
+                     workspace)
 from test_gpu_step import _oracle_step, _run_step
 
 pytestmark = pytest.mark.gpu
@@ -84,3 +85,32 @@ def test_vt_rows_at_every_alignment():
     vel, _, _ = _run_step(m, params, shapes, cfg, grids, n_txt, ts, lat, txt)
     ref = np.concatenate(_oracle_step(m, params, grids, n_txt, ts, lat, txt))
     assert normwise_err(vel.float().cpu().numpy(), ref) < BF16_TOL
+
+
+@pytest.mark.parametrize("head_dim", [64, 128])
+@pytest.mark.parametrize("grids,n_txt", [
+    ([(1, 1), (16, 16)], [62, 0]),   # rows 32..61 text at 33..62, row 62 image at 0, row 63 the next request's at 64
+    ([(2, 5), (16, 16)], [44, 0]),
+    ([(3, 1), (3, 1), (16, 16)], [85, 55, 0]),
+])
+def test_vt_where_text_rows_run_into_image_rows(grids, n_txt, head_dim):
+    """Single blocks whose 32-row groups cross from text to image with ends as far apart as consecutive rows
+    would be: every request's velocity against the oracle, on a workspace filled with NaN."""
+    import torch
+    m = workloads.ModelShape(hidden=256, heads=256 // head_dim, head_dim=head_dim, mlp_ratio=2, n_double=0, n_single=2,
+                             in_channels=64, text_dim=64)
+    cfg, shapes, params = host_params(m, 15)
+    ts = [0.2 * (i + 1) for i in range(len(grids))]
+    lat, txt = request_inputs(m, grids, n_txt, 15)
+    w = upload_params(params, shapes, torch.bfloat16)
+    b = dit.Batch([g[0] for g in grids], [g[1] for g in grids], n_txt, ts)
+    ws, nws = workspace(cfg, b)
+    ws.fill_(255)
+    x, e = to_dev(np.concatenate(lat), torch.bfloat16), to_dev(np.concatenate(txt), torch.bfloat16)
+    vel = torch.full_like(x, float("nan"))
+    dit.dit_step(cfg, w, b, x, e, vel, ws, nws)
+    torch.cuda.synchronize()
+    got, off = vel.float().cpu().numpy(), 0
+    for r, ref in enumerate(_oracle_step(m, params, grids, n_txt, ts, lat, txt)):
+        assert normwise_err(got[off:off + len(ref)], ref) < BF16_TOL, r
+        off += len(ref)
