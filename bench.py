@@ -519,7 +519,7 @@ def main() -> int:
                         "tflops": v["flops"] / (v["ms"] / 1e3) / 1e12, "gbs": v["bytes"] / (v["ms"] / 1e3) / 1e9}
                     for k, v in main_res["kernels"].items() if not k.startswith("detail:")},
         "gemm_shapes": {k[7:]: {"ms_per_step": round(v["ms_per_step"], 4), "tflops": round(v["flops"] / (v["ms"] / 1e3) / 1e12, 1)}
-                        for k, v in main_res["kernels"].items() if k.startswith("detail:")},
+                        for k, v in main_res["kernels"].items() if k.startswith("detail:gemm")},
     }
     print(json.dumps(out), flush=True)
     return 0

@@ -225,9 +225,15 @@ dit_status euler_update(const dit_batch* batch, int channels, int dtype, void* l
  * at head_dim 128, when the last round of 128-query tiles (two per CU) is at
  * most a quarter full after two or more full rounds and every request has one
  * length, the fp32 partial results of those tiles' key ranges (up to 33 MiB),
- * merged in a fixed order (bitwise repeatable).  With a workspace of 66 MiB
- * more than V^T, DIT_BF16 at head_dim 128 may instead share out all key tiles
- * past the last full round of 256-query tiles evenly, where that is faster.
+ * merged in a fixed order (bitwise repeatable).  Those calls apart, a request's
+ * output bits do not depend on what it is packed with, unless the caller gives a
+ * workspace of V^T plus 66 MiB or more.  A DIT_BF16 call may then, where it is
+ * faster, share out all key tiles past the last full round of 256-query tiles
+ * evenly (head_dim 128), and split the keys of each query tile over two wave
+ * groups when the launch has at most 256 query tiles and a request of 1280 keys
+ * or more.  Both orders of sums are fixed too (bitwise repeatable), but they
+ * follow from the whole batch.  To keep bits independent of the batch, pass
+ * ws_bytes as reported, however large the buffer is.
  */
 dit_status dit_attention_workspace_size(const dit_batch* batch, int heads, int head_dim, int dtype,
                                         size_t* bytes);

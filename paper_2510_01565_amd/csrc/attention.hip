@@ -846,7 +846,7 @@ struct StreamPlan {
   int main_units;
 };
 
-size_t stream_bytes(int head_dim) { return (size_t)2 * kStreamBlocks * 256 * (head_dim + 2) * sizeof(float); }
+static_assert(kAttnShareBytes >= (size_t)2 * kStreamBlocks * 256 * (128 + 2) * sizeof(float), "slots of the runs' ends");
 
 bool stream_plan(const BatchMeta& m, int heads, int head_dim, StreamPlan* out) {
   if (head_dim != 128) return false;
@@ -941,11 +941,46 @@ bool wide_64(long units, long units8) {
   return wide < narrow;
 }
 
+// What a launch runs: its last query tiles' keys shared out evenly (stream
+// plan), the keys of a short last round split (split plan), two key groups per
+// block, or plain blocks of 256 or 128 queries.
+enum AttnCfg { ATTN_SHARED = 0, ATTN_KEY_SPLIT, ATTN_KEY_GROUPS, ATTN_256, ATTN_128 };
+
+AttnCfg pick_attn(const AttnArgs& a, StreamPlan* stream, SplitPlan* split) {
+  if (a.split_buf && a.split_bytes >= kAttnShareBytes && stream_plan(a.meta, a.heads, a.head_dim, stream))
+    return ATTN_SHARED;
+  *split = split_plan(a.meta, a.heads, a.head_dim);
+  if (split->pieces && a.split_buf && a.split_bytes >= split_bytes(*split, a.head_dim)) return ATTN_KEY_SPLIT;
+  const AttnSched sc4 = make_sched(a.meta, 4 * 32);
+  const long units = (long)sc4.tile_off[sc4.n] * a.heads;
+  bool equal = true;
+  const int L0 = a.meta.joint_off[sc4.req[0] + 1] - a.meta.joint_off[sc4.req[0]];
+  for (int i = 1; i < sc4.n; ++i)
+    equal = equal && a.meta.joint_off[sc4.req[i] + 1] - a.meta.joint_off[sc4.req[i]] == L0;
+  // the 256-query launch's own block count (not units / 2 when a request has
+  // an odd number of 128-query tiles) and the fill of its last round
+  const AttnSched sc8 = make_sched(a.meta, 8 * 32);
+  const long units8 = (long)sc8.tile_off[sc8.n] * a.heads;
+  constexpr long kSlots8 = 256;  // 256-query blocks resident per GPU at head dim 128 (one per CU)
+  const long last8 = units8 % kSlots8;
+  const bool wide = a.head_dim == 128 ? equal && (last8 == 0 || 2 * last8 > kSlots8)
+                                      : wide_64(units, units8) && (equal || units8 <= 512);
+  // Two key groups per block where every block has a CU to itself and at least
+  // 20 key tiles: 168 units x 28 tiles 62.6 -> 52.2 us at head dim 128 and 42.6
+  // -> 36.9 at 64, 240 x 40 88.7 -> 81.4 and 57.5 -> 51.6, 240 x 20 32.2 -> 31.1
+  // and 21.9 -> 21.3; equal at 12 tiles and up to 12% slower below (the second
+  // group's tiles and the merge), equal or slower with more than 256 units.
+  if (a.allow_split && units <= 256 && L0 >= 20 * kKeyTile) return ATTN_KEY_GROUPS;
+  return wide ? ATTN_256 : ATTN_128;
+}
+
 template <int HD>
 hipError_t launch_attn_hd(const AttnArgs& a, hipStream_t s) {
+  StreamPlan p;
+  SplitPlan sp;
+  const AttnCfg cfg = pick_attn(a, &p, &sp);
   if constexpr (HD == 128) {
-    StreamPlan p;
-    if (a.split_buf && a.split_bytes >= stream_bytes(HD) && stream_plan(a.meta, a.heads, HD, &p)) {
+    if (cfg == ATTN_SHARED) {
       if (p.main_units) {
         AttnSched main = p.sc;
         main.n = p.st.slot0[1];
@@ -961,46 +996,24 @@ hipError_t launch_attn_hd(const AttnArgs& a, hipStream_t s) {
                          p.st);
       return hipGetLastError();
     }
+    if (cfg == ATTN_KEY_SPLIT) {
+      const AttnSched sc = make_sched(a.meta, 128);
+      AttnArgs b = a;
+      b.unit0 = 0;
+      b.units = sp.main_units;
+      b.kv_pieces = 1;
+      hipLaunchKernelGGL((attn_bf16_kernel<4, HD, 2, kKeyTile, 1>), dim3((unsigned)sp.main_units), dim3(256), 0, s, b, sc);
+      b.unit0 = sp.main_units;
+      b.units = sp.tail_units;
+      b.kv_pieces = sp.pieces;
+      hipLaunchKernelGGL((attn_bf16_kernel<4, HD, 2, kKeyTile, 1>), dim3((unsigned)(sp.tail_units * sp.pieces)), dim3(256),
+                         0, s, b, sc);
+      hipLaunchKernelGGL((attn_merge_kernel<HD>), dim3((unsigned)sp.tail_units), dim3(256), 0, s, b, sc);
+      return hipGetLastError();
+    }
   }
-  const SplitPlan sp = a.split_buf && a.split_bytes >= split_bytes(split_plan(a.meta, a.heads, HD), HD)
-                           ? split_plan(a.meta, a.heads, HD)
-                           : SplitPlan{0, 0, 0};
-  if (sp.pieces) {
-    const AttnSched sc = make_sched(a.meta, 128);
-    AttnArgs b = a;
-    b.unit0 = 0;
-    b.units = sp.main_units;
-    b.kv_pieces = 1;
-    hipLaunchKernelGGL((attn_bf16_kernel<4, HD, 2, kKeyTile, 1>), dim3((unsigned)sp.main_units), dim3(256), 0, s, b, sc);
-    b.unit0 = sp.main_units;
-    b.units = sp.tail_units;
-    b.kv_pieces = sp.pieces;
-    hipLaunchKernelGGL((attn_bf16_kernel<4, HD, 2, kKeyTile, 1>), dim3((unsigned)(sp.tail_units * sp.pieces)), dim3(256), 0, s, b,
-                       sc);
-    hipLaunchKernelGGL((attn_merge_kernel<HD>), dim3((unsigned)sp.tail_units), dim3(256), 0, s, b, sc);
-    return hipGetLastError();
-  }
-  const AttnSched sc4 = make_sched(a.meta, 4 * 32);
-  const long units = (long)sc4.tile_off[sc4.n] * a.heads;
-  bool equal = true;
-  const int L0 = a.meta.joint_off[sc4.req[0] + 1] - a.meta.joint_off[sc4.req[0]];
-  for (int i = 1; i < sc4.n; ++i)
-    equal = equal && a.meta.joint_off[sc4.req[i] + 1] - a.meta.joint_off[sc4.req[i]] == L0;
-  // the 256-query launch's own block count (not units / 2 when a request has
-  // an odd number of 128-query tiles) and the fill of its last round
-  const AttnSched sc8 = make_sched(a.meta, 8 * 32);
-  const long units8 = (long)sc8.tile_off[sc8.n] * a.heads;
-  constexpr long kSlots8 = 256;  // 256-query blocks resident per GPU at head dim 128 (one per CU)
-  const long last8 = units8 % kSlots8;
-  const bool wide = HD == 128 ? equal && (last8 == 0 || 2 * last8 > kSlots8)
-                              : wide_64(units, units8) && (equal || units8 <= 512);
-  // Two key groups per block where every block has a CU to itself and at least
-  // 20 key tiles: 168 units x 28 tiles 62.6 -> 52.2 us at head dim 128 and 42.6
-  // -> 36.9 at 64, 240 x 40 88.7 -> 81.4 and 57.5 -> 51.6, 240 x 20 32.2 -> 31.1
-  // and 21.9 -> 21.3; equal at 12 tiles and up to 12% slower below (the second
-  // group's tiles and the merge), equal or slower with more than 256 units.
-  if (a.allow_split && units <= 256 && L0 >= 20 * kKeyTile) return launch_attn_cfg<4, HD, 2>(a, s);
-  if (wide) return launch_attn_cfg<8, HD>(a, s);
+  if (cfg == ATTN_KEY_GROUPS) return launch_attn_cfg<4, HD, 2>(a, s);
+  if (cfg == ATTN_256) return launch_attn_cfg<8, HD>(a, s);
   return launch_attn_cfg<4, HD>(a, s);
 }
 
@@ -1008,6 +1021,14 @@ hipError_t launch_attention_bf16(const AttnArgs& a, hipStream_t s) {
   if (a.head_dim == 128) return launch_attn_hd<128>(a, s);
   if (a.head_dim == 64) return launch_attn_hd<64>(a, s);
   return hipErrorInvalidValue;
+}
+
+const char* attention_bf16_config_name(const AttnArgs& a) {
+  static const char* names[] = {"attention_bf16_shared", "attention_bf16_key_split", "attention_bf16_key_groups",
+                                "attention_bf16_256", "attention_bf16_128"};
+  StreamPlan p;
+  SplitPlan sp;
+  return names[pick_attn(a, &p, &sp)];
 }
 
 size_t attn_split_bytes(const BatchMeta& m, int heads, int head_dim) {

@@ -379,9 +379,19 @@ double attn_flops(const BatchMeta& m, int heads, int d) {
 
 hipError_t attn_launch(hipStream_t s, int dtype, const AttnArgs& a) {
   const double bytes = 4.0 * a.meta.T * (double)a.heads * a.head_dim * (dtype == DIT_BF16 ? 2 : 4);
-  if (dtype == DIT_BF16)
-    return timed(s, "attention_bf16", attn_flops(a.meta, a.heads, a.head_dim), bytes,
-                 [&] { return launch_attention_bf16(a, s); });
+  if (dtype == DIT_BF16) {
+    if (!prof().on) return launch_attention_bf16(a, s);
+    // the family, and an entry ("detail:" prefix) that names the plan the call took
+    char detail[64];
+    snprintf(detail, sizeof(detail), "detail:%s", attention_bf16_config_name(a));
+    const double flops = attn_flops(a.meta, a.heads, a.head_dim);
+    hipError_t e = hipSuccess;
+    hipError_t r = timed(s, detail, flops, bytes, [&] {
+      e = timed(s, "attention_bf16", flops, bytes, [&] { return launch_attention_bf16(a, s); });
+      return e;
+    });
+    return r != hipSuccess ? r : e;
+  }
   return timed(s, "attention_f32", attn_flops(a.meta, a.heads, a.head_dim), bytes,
                [&] { return launch_attention_f32(a, s); });
 }
@@ -959,11 +969,13 @@ dit_status dit_attention(const dit_batch* batch, int heads, int head_dim, int dt
     a.vt_off[r] = m.pad_off[r];
   }
   a.meta = m;
-  a.allow_split = 1;
   if (dtype == DIT_BF16 && ws_bytes > vt_bytes) {
     a.split_buf = (float*)((char*)ws + vt_bytes);
     a.split_bytes = ws_bytes - vt_bytes;
   }
+  // The call has no flags: a workspace well above the reported size is the
+  // caller's leave for plans whose sums depend on the batch.
+  a.allow_split = a.split_bytes >= kAttnShareBytes;
   HIP_TRY(attn_launch(s, dtype, a));
   return DIT_OK;
 }

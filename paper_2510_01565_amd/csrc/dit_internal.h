@@ -209,12 +209,13 @@ struct AttnArgs {
   int vt_off[kMaxReq + 1];
   BatchMeta meta;
   // Scratch of split_bytes bytes for sharing out the key tiles of a launch's
-  // last rounds (bf16, head dim 128), or null (never split; the output bits
-  // then do not depend on how many other tiles share the launch).  The key
-  // split of a short last round needs attn_split_bytes(), even sharing 65 MiB.
+  // last rounds (bf16, head dim 128), or null (never shared out).  The key split
+  // of a short last round needs attn_split_bytes(), even sharing kAttnShareBytes.
   float* split_buf;
   size_t split_bytes;
-  // whether the order of a query's sums may depend on how many tiles the launch has
+  // Whether a launch of few query tiles may give a block two key groups.  Unset
+  // and without split_buf, the order of a query's sums, and so its output bits,
+  // do not depend on how many other tiles share the launch.
   int allow_split;
   // set by the launcher: this launch covers query-tile units
   // [unit0, unit0 + units); kv_pieces > 1 splits each unit's keys into that
@@ -222,6 +223,11 @@ struct AttnArgs {
   int unit0, units, kv_pieces;
 };
 hipError_t launch_attention_bf16(const AttnArgs& a, hipStream_t s);
+// name of the plan launch_attention_bf16 picks for a
+const char* attention_bf16_config_name(const AttnArgs& a);
+// scratch of evenly shared key tiles: the two ends of 256 runs, each of 256
+// queries x 128 dimensions in fp32 with their maxima and sums
+constexpr size_t kAttnShareBytes = 65 << 20;
 // bytes of split_buf for the key split of a short last round (0: it does not apply)
 size_t attn_split_bytes(const BatchMeta& m, int heads, int head_dim);
 hipError_t launch_attention_f32(const AttnArgs& a, hipStream_t s);

@@ -4,10 +4,21 @@ import numpy as np
 import pytest
 
 import oracle as O
-from paper_2510_01565_amd import dit, synth
+from paper_2510_01565_amd import dit, synth, workloads
 from harness import BF16_TOL, normwise_err, to_dev
 
 pytestmark = pytest.mark.gpu
+
+SHARE_BYTES = 66 << 20  # past V^T: leave for plans whose sums depend on the batch
+
+
+def _vt_bytes(lens, heads, d):
+    return (heads * d * sum((L + 63) // 64 * 64 for L in lens) * 2 + 255) // 256 * 256
+
+
+def _plans(profile):
+    """The attention plans of a profiled run."""
+    return {k.rsplit("attention_bf16_", 1)[1] for k in profile if k.startswith("detail:attention_bf16_")}
 
 
 @pytest.mark.parametrize("grids,n_txt,heads", [
@@ -40,12 +51,14 @@ def test_attention_d64_dispatch(grids, n_txt, heads):
 
 @pytest.mark.parametrize("d", [128, 64])
 @pytest.mark.parametrize("gain", [1.0, 16.0])
-@pytest.mark.parametrize("grids,n_txt,heads", [
-    ([(31, 41)], [0], 3),                  # 1271 keys: 20 tiles, 10 for each key group, the last one ragged
-    ([(32, 42)], [0], 2),                  # 1344: 21 tiles, 11 and 10
-    ([(36, 36), (1, 1), (8, 16)], [3, 0, 1], 2),  # 21 tiles, one tile (no second group), 3 tiles
+@pytest.mark.parametrize("grids,n_txt,heads,plan", [
+    ([(31, 41)], [0], 3, "128"),                  # 1271 keys, fewer than 20 whole tiles: no groups
+    ([(32, 40)], [0], 3, "key_groups"),           # 1280: 20 tiles, 10 for each key group
+    ([(31, 42)], [0], 3, "key_groups"),           # 1302: 21 tiles, 11 and 10, the last one ragged
+    ([(32, 42)], [0], 2, "key_groups"),           # 1344: 21 tiles, 11 and 10
+    ([(36, 36), (1, 1), (8, 16)], [3, 0, 1], 2, "key_groups"),  # 21 tiles, one tile (no second group), 3 tiles
 ])
-def test_attention_key_groups(grids, n_txt, heads, d, gain):
+def test_attention_key_groups(grids, n_txt, heads, plan, d, gain):
     """Few long query tiles: two wave groups share a block's keys; logits up to hundreds put their maxima
     far apart.  Every row against the oracle, and the same bits on a second call."""
     import torch
@@ -54,14 +67,16 @@ def test_attention_key_groups(grids, n_txt, heads, d, gain):
     qb, kb = (torch.from_numpy((synth.normal(32, n, (T, heads, d)) * np.float32(gain ** 0.5))).to(torch.bfloat16) for n in "qk")
     v = synth.normal(32, "v", (T, heads, d), bf16=True)
     b = dit.Batch([g[0] for g in grids], [g[1] for g in grids], n_txt)
-    wsb = dit.attention_workspace_size(b, heads, d, dit.DIT_BF16)
+    wsb = _vt_bytes(lens, heads, d) + SHARE_BYTES
     ws = torch.empty(wsb, dtype=torch.uint8, device="cuda")
     outs = []
+    dit.profile_start()
     for _ in range(2):
         o = torch.full((T, heads, d), float("nan"), dtype=torch.bfloat16, device="cuda")
         dit.dit_attention(b, heads, d, dit.DIT_BF16, qb.cuda(), kb.cuda(), to_dev(v, torch.bfloat16), o, ws, wsb)
         torch.cuda.synchronize()
         outs.append(o)
+    assert _plans(dit.profile_stop()) == {plan}
     assert torch.equal(outs[0], outs[1])
     got, off = outs[0].float().cpu().numpy(), 0
     q64, k64 = qb.float().numpy().astype(np.float64), kb.float().numpy().astype(np.float64)
@@ -82,12 +97,12 @@ def test_attention_evenly_shared_keys(grids, n_txt, heads, shared):
     bits on a second call, and the plan of a workspace without room for the runs' parts."""
     import torch
     d, lens = 128, [gh * gw + nt for (gh, gw), nt in zip(grids, n_txt)]
-    T, Tp = sum(lens), sum((L + 63) // 64 * 64 for L in lens)
+    T = sum(lens)
     gen = torch.Generator(device="cuda").manual_seed(33)
     q, k, v = (torch.randn((T, heads, d), generator=gen, device="cuda", dtype=torch.bfloat16) for _ in range(3))
     b = dit.Batch([g[0] for g in grids], [g[1] for g in grids], n_txt)
     wsb = dit.attention_workspace_size(b, heads, d, dit.DIT_BF16)
-    big = (heads * d * Tp * 2 + 255) // 256 * 256 + (66 << 20)
+    big = _vt_bytes(lens, heads, d) + SHARE_BYTES
     outs = []
     for n in (big, big, wsb):
         ws = torch.full((n,), 255, dtype=torch.uint8, device="cuda")  # stale parts are NaN
@@ -111,3 +126,72 @@ def test_attention_evenly_shared_keys(grids, n_txt, heads, shared):
             ref = O.attention(*x, rows=rows)
             assert normwise_err(outs[0][sl, h:h + 1].float().cpu().numpy()[rows], ref) < BF16_TOL
         off += L
+
+
+@pytest.mark.parametrize("d", [128, 64])
+def test_attention_bits_do_not_depend_on_the_batch(d):
+    """At the reported workspace size a request of 1344 keys has the same bits alone (33 query tiles) and packed
+    (more than 256), at both ends of the batch."""
+    import torch
+    heads, grids, n_txt = 3, [(32, 42), (64, 64), (64, 66), (64, 63), (32, 42)], [0, 0, 5, 512, 0]
+    lens = [gh * gw + nt for (gh, gw), nt in zip(grids, n_txt)]
+    assert sum((L + 127) // 128 for L in lens) * heads > 256
+    gen = torch.Generator(device="cuda").manual_seed(34)
+    q, k, v = (torch.randn((sum(lens), heads, d), generator=gen, device="cuda", dtype=torch.bfloat16) for _ in range(3))
+
+    def run(rs, sl):
+        b = dit.Batch([grids[r][0] for r in rs], [grids[r][1] for r in rs], [n_txt[r] for r in rs])
+        n = dit.attention_workspace_size(b, heads, d, dit.DIT_BF16)
+        ws = torch.empty(n, dtype=torch.uint8, device="cuda")
+        x = [t[sl].contiguous() for t in (q, k, v)]
+        o = torch.full_like(x[0], float("nan"))
+        dit.dit_attention(b, heads, d, dit.DIT_BF16, *x, o, ws, n)
+        torch.cuda.synchronize()
+        return o
+
+    packed, off = run(range(len(lens)), slice(None)), 0
+    assert torch.isfinite(packed).all()
+    for r, L in enumerate(lens):
+        sl = slice(off, off + L)
+        assert torch.equal(run([r], sl), packed[sl]), r
+        off += L
+
+
+@pytest.mark.parametrize("head_dim", [128, 64])
+@pytest.mark.parametrize("kind", [0, 1])
+def test_batch_invariant_block_keeps_key_groups_out(kind, head_dim):
+    """A request of 1344 tokens and few heads: alone its attention would run two key groups per block, packed it
+    has more than 256 query tiles.  Batch-invariant blocks give it the same bits in both."""
+    import torch
+    heads = 4
+    m = workloads.ModelShape(hidden=heads * head_dim, heads=heads, head_dim=head_dim, mlp_ratio=1, n_double=1 - kind,
+                             n_single=kind, in_channels=64, text_dim=64)
+    grids, n_txt = [(36, 36), (64, 64), (60, 64)], [48, 100, 0]
+    H, lens = m.hidden, [gh * gw + nt for (gh, gw), nt in zip(grids, n_txt)]
+    assert lens[0] == 1344 and sum((L + 127) // 128 for L in lens) * heads > 256
+    gen = torch.Generator(device="cuda").manual_seed(35)
+    w = dit.Weights([torch.randn(s, generator=gen, device="cuda").mul_(0.05).to(torch.bfloat16)
+                     for _, s in dit.weight_manifest(dit.make_config(m))])
+    txt = [torch.randn((n, H), generator=gen, device="cuda") for n in n_txt]
+    img = [torch.randn((gh * gw, H), generator=gen, device="cuda") for gh, gw in grids]
+    cond = torch.randn((len(lens), H), generator=gen, device="cuda")
+
+    def run(rs, flags):
+        cfg = dit.make_config(m, flags)
+        b = dit.Batch([grids[r][0] for r in rs], [grids[r][1] for r in rs], [n_txt[r] for r in rs])
+        n = dit.workspace_size(cfg, b)
+        ws = torch.empty(n, dtype=torch.uint8, device="cuda")
+        hidden = torch.cat([txt[r] for r in rs] + [img[r] for r in rs])
+        dit.profile_start()
+        dit.dit_block_forward(cfg, w, kind, 0, b, hidden, cond[rs].contiguous(), ws, n)
+        torch.cuda.synchronize()
+        return hidden, _plans(dit.profile_stop())
+
+    assert run([0], 0)[1] == {"key_groups"}
+    alone, plans = run([0], dit.DIT_FLAG_BATCH_INVARIANT)
+    assert plans == {"128"}
+    packed, _ = run([0, 1, 2], dit.DIT_FLAG_BATCH_INVARIANT)
+    T = sum(n_txt)
+    assert torch.isfinite(packed).all()
+    assert torch.equal(alone[:n_txt[0]], packed[:n_txt[0]])
+    assert torch.equal(alone[n_txt[0]:], packed[T:T + 36 * 36])
