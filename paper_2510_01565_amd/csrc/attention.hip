@@ -14,6 +14,7 @@
 // chunks); the softmax runs in the log2 domain (exp2 with log2(e)/sqrt(d)
 // folded into the scale).  Blocks of one head are mapped onto one XCD so its
 // K/V tiles are shared through that XCD's L2.
+#include <float.h>
 #include <math.h>
 
 #include <algorithm>
@@ -172,7 +173,10 @@ __device__ __forceinline__ void attn_unit(const AttnArgs& a, char* smem, int r, 
   for (int db = 0; db < HD / 32; ++db)
 #pragma unroll
     for (int i = 0; i < 16; ++i) o[db][i] = 0.f;
-  float m_i = -INFINITY, l_i = 0.f;
+  // The running max starts at the lowest finite value: a range of keys whose
+  // scores are all -inf then adds nothing (from -inf it would give -inf - -inf),
+  // wherever the query's keys are cut into ranges.
+  float m_i = -FLT_MAX, l_i = 0.f;
   const float sl2 = a.scale * 1.4426950408889634f;
 
   // S^T of one 64-key tile: two 32x32 blocks (keys kb*32 + (i/4)*8 + hl*4 + i%4 of
@@ -344,7 +348,7 @@ __device__ __forceinline__ void attn_unit(const AttnArgs& a, char* smem, int r, 
     }
     __syncthreads();
     if (kg == 1) return;
-    // a group without a tile has max -inf, sum 0 and O 0
+    // a group without a tile has the lowest max, sum 0 and O 0
     const float m1 = sh[NR * 64], mm = fmaxf(m_i, m1);
     const float a0 = __builtin_amdgcn_exp2f(m_i - mm), a1 = __builtin_amdgcn_exp2f(m1 - mm);
     m_i = mm;
@@ -667,7 +671,7 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(const AttnArgs a, const A
     return e == 0 ? v.x : e == 1 ? v.y : e == 2 ? v.z : v.w;
   };
   const float sl2 = a.scale * kLog2e;
-  float m = -INFINITY, l = 0.f;  // m: of the query, in the log2 domain; l: of this lane's keys
+  float m = -FLT_MAX, l = 0.f;   // m: of the query, in the log2 domain, finite (see attn_unit); l: of this lane's keys
   f32x4_t o[4] = {};             // O^T rows 16 c + 4 kq .. + 3 of query lr
   if (t0 < t1) {
     load_k(t0);
@@ -690,7 +694,7 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(const AttnArgs a, const A
       mx = fmaxf(mx, s[i]);
     }
     mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));  // finite: the tile holds at least one key
+    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
     const float al = exp2f(m - mx);
     m = mx;
     l *= al;
@@ -716,7 +720,7 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(const AttnArgs a, const A
 #pragma unroll
   for (int c = 0; c < 4; ++c) *(float4*)&osh[wave][lr][c * 16 + kq * 4] = make_float4(o[c][0], o[c][1], o[c][2], o[c][3]);
   __syncthreads();
-  // 16 lanes per query, 4 dims each.  A wave without a tile has max -inf and
+  // 16 lanes per query, 4 dims each.  A wave without a tile has the lowest max and
   // weighs nothing; wave 3 always has one.
   const int ql = tid >> 4, dd = (tid & 15) * 4, qrow = q0 + ql;
   if (qrow >= L) return;

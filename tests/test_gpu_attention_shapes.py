@@ -5,7 +5,7 @@ import pytest
 
 import oracle as O
 from paper_2510_01565_amd import dit, synth, workloads
-from harness import BF16_TOL, normwise_err, to_dev
+from harness import BF16_TOL, F32_TOL, normwise_err, to_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -195,3 +195,43 @@ def test_batch_invariant_block_keeps_key_groups_out(kind, head_dim):
     assert torch.isfinite(packed).all()
     assert torch.equal(alone[:n_txt[0]], packed[:n_txt[0]])
     assert torch.equal(alone[n_txt[0]:], packed[T:T + 36 * 36])
+
+
+@pytest.mark.parametrize("bf16,d,grid,n_txt,heads,cut,plan", [
+    (False, 64, (16, 16), 32, 2, [(64, 80), (128, 176), (256, 288)], None),  # first tiles of the waves, the last tile
+    (False, 64, (5, 7), 0, 1, [(0, 16), (32, 35)], None),                    # waves of one tile each
+    (True, 128, (32, 42), 0, 2, [(704, 768)], "key_groups"),    # the second group's first tile
+    (True, 64, (32, 42), 0, 2, [(704, 1344)], "key_groups"),    # all of the second group
+    (True, 64, (32, 42), 0, 2, [(0, 704)], "key_groups"),       # all of the first
+    (True, 128, (128, 128), 512, 6, [(4000, 16896)], "shared"),  # most runs' whole shares
+    (True, 128, (16, 16), 0, 2, [(0, 64), (128, 256)], "128"),  # the first tile of a plain block
+])
+def test_attention_keys_without_weight(bf16, d, grid, n_txt, heads, cut, plan):
+    """Keys whose scores are -inf for every query (a coordinate of -inf against a positive one) have weight zero,
+    also where they fill a wave's, a group's or a run's first tiles: the result is attention over the other keys."""
+    import torch
+    L = grid[0] * grid[1] + n_txt
+    dt = torch.bfloat16 if bf16 else torch.float32
+    gen = torch.Generator(device="cuda").manual_seed(36)
+    q, k, v = (torch.randn((L, heads, d), generator=gen, device="cuda").to(dt) for _ in range(3))
+    q[..., 0] = 1.0
+    keep = torch.ones(L, dtype=torch.bool, device="cuda")
+    for a, e in cut:
+        k[a:e, :, 0] = float("-inf")
+        keep[a:e] = False
+    b = dit.Batch([grid[0]], [grid[1]], [n_txt])
+    et = dit.DIT_BF16 if bf16 else dit.DIT_F32
+    n = _vt_bytes([L], heads, d) + SHARE_BYTES if bf16 else dit.attention_workspace_size(b, heads, d, et)
+    ws, o = torch.empty(n, dtype=torch.uint8, device="cuda"), torch.full_like(q, float("nan"))
+    dit.profile_start()
+    dit.dit_attention(b, heads, d, et, q, k, v, o, ws, n)
+    torch.cuda.synchronize()
+    plans = _plans(dit.profile_stop())
+    assert plans == ({plan} if plan else set())
+    rows = np.unique(np.concatenate([np.arange(0, L, 131), [L - 1]]))
+    for h in range(heads):
+        qh, kh, vh = (x[:, h].double().cpu().numpy() for x in (q, k[keep], v[keep]))
+        s = qh[rows] @ kh.T / np.sqrt(d)
+        p = np.exp(s - s.max(axis=1, keepdims=True))
+        ref = (p / p.sum(axis=1, keepdims=True)) @ vh
+        assert normwise_err(o[:, h].float().cpu().numpy()[rows], ref) < (BF16_TOL if bf16 else F32_TOL)
