@@ -20,7 +20,6 @@
 
 #include "device_common.h"
 
-
 namespace dit {
 
 namespace {
@@ -98,19 +97,32 @@ __device__ __forceinline__ void asm_lgkm_wait() {
   if constexpr (N < 15) asm volatile("s_waitcnt lgkmcnt(%0)" ::"i"(N));
 }
 
+// ON: v, of an origin unknown to the compiler, so that what is computed from it
+// stays in the branch that asks for it instead of moving ahead of that branch.
+template <bool ON>
+__device__ __forceinline__ int opaque(int v) {
+  if constexpr (ON) asm volatile("" : "+v"(v));
+  return v;
+}
+
 // One staged group of 32 rows x W columns of a tile, corner (m, n), bias added
 // (staging pitch W + 4 floats).  Consecutive lanes take consecutive 16-byte
 // pieces of an output row, so a wave's access covers whole runs of W columns;
 // a lane's loads all leave before its first store (one in-order counter holds
-// both).  H and the head dimension are multiples of 64 and n and W of 16, so
-// an 8-column piece lies in one head of one of Q, K, V or the MLP input, but a
-// group of 48 columns need not.
-template <int W>
+// both).  H is a multiple of 64, the head dimension 64 or 128, and n and W are
+// multiples of 16, so an 8-column piece lies in one head of one of Q, K, V or the
+// MLP input, but a group of 48 columns need not.
+// FAST: for group loops that are unrolled (see the kernel's epilogue).  m and n
+// are scalars and with them the branches, no mode's address arithmetic runs for
+// another mode, and whole groups of plain columns leave LDS entirely before they
+// are stored, without a branch between their pieces.
+template <int W, bool FAST>
 __device__ __forceinline__ void epilogue_group(const EpiArgs& E, const RowEntry* rows, const float* stg, int m, int n,
                                                int M, int N, int lane) {
   constexpr int SP = W + 4;
   if (n >= N || m >= M) return;
   const int v0 = E.mode == EPI_QKV ? 2 * E.hidden : N, v1 = E.mode == EPI_QKV ? 3 * E.hidden : N;  // V columns
+  const int hs = E.head_dim == 128 ? 7 : 6;  // its logarithm: 128 or 64 in bf16
   if (n < v1 && n + W > v0) {
     // A lane takes one column of the group.  Rows at consecutive positions of
     // one request are consecutive keys of V^T: two 16-key groups (four 16-byte
@@ -119,8 +131,8 @@ __device__ __forceinline__ void epilogue_group(const EpiArgs& E, const RowEntry*
     // multiple of 16 leave every later row unaligned; with a 2-byte store per
     // key a QKV launch of 8056 x 21504 x 3072 (67 x 116 image) took 896 us between
     // events, now 826, and 24 of 3414 x 4608 x 1536 93 -> 68 us each.
-    const int hn = n + lane - v0, h = hn / E.head_dim, dd = hn - h * E.head_dim;
-    if (lane < W && n + lane >= v0 && n + lane < v1 && n + lane < N) {
+    const int ln = opaque<FAST>(lane), hn = n + ln - v0, h = hn >> hs, dd = hn - h * E.head_dim;
+    if (ln < W && n + ln >= v0 && n + ln < v1 && n + ln < N) {
       bf16_t* vt = (bf16_t*)E.vt + ((long)h * E.head_dim + dd) * E.vt_ld;
       const int p0 = rows[0].pos;
       if (m + 31 < M && rows_consecutive(rows[0], rows[31], 32)) {
@@ -130,13 +142,13 @@ __device__ __forceinline__ void epilogue_group(const EpiArgs& E, const RowEntry*
             // slot s of a group holds key vt_slot(s): swap the middle quads
             float w[16];
 #pragma unroll
-            for (int q = 0; q < 16; ++q) w[q] = stg[(r16 + vt_slot(q)) * SP + lane];
+            for (int q = 0; q < 16; ++q) w[q] = stg[(r16 + vt_slot(q)) * SP + ln];
             store16<bf16_t>(vt + p0 + r16, w);
           }
         } else {
           const int a = -p0 & 3;  // rows ahead of the first whole quad
-          const float* col = stg + a * SP + lane;
-          for (int q = 0; q < a; ++q) vt[vt_slot(p0 + q)] = f2bf(stg[q * SP + lane]);
+          const float* col = stg + a * SP + ln;
+          for (int q = 0; q < a; ++q) vt[vt_slot(p0 + q)] = f2bf(stg[q * SP + ln]);
 #pragma unroll
           for (int t = 0; t < 8; ++t) {
             if (t == 7 && a > 0) break;
@@ -145,22 +157,52 @@ __device__ __forceinline__ void epilogue_group(const EpiArgs& E, const RowEntry*
             w.y = pack_bf16x2(col[(4 * t + 2) * SP], col[(4 * t + 3) * SP]);
             *(uint2*)(vt + vt_slot(p0 + a + 4 * t)) = w;
           }
-          for (int q = 28 + a; a > 0 && q < 32; ++q) vt[vt_slot(p0 + q)] = f2bf(stg[q * SP + lane]);
+          for (int q = 28 + a; a > 0 && q < 32; ++q) vt[vt_slot(p0 + q)] = f2bf(stg[q * SP + ln]);
         }
       } else {
-        for (int q = 0; q < 32 && m + q < M; ++q) vt[vt_slot(rows[q].pos)] = f2bf(stg[q * SP + lane]);
+        for (int q = 0; q < 32 && m + q < M; ++q) vt[vt_slot(rows[q].pos)] = f2bf(stg[q * SP + ln]);
       }
     }
     if (n >= v0 && n + W <= v1) return;
   }
   if (E.mode == EPI_RESID || E.mode == EPI_STORE_F32) {
     constexpr int PPR = W / 4, NP = 16 * PPR / 64;  // 16-byte pieces of a row, pieces of a lane in half the rows
+    const int ln = opaque<FAST>(lane);
     float* const o = (float*)E.out + (long)m * E.ldo + n;
     const int last = M - 1 - m, cols = N - n;
+    if constexpr (FAST) {
+      if (E.mode == EPI_STORE_F32) {
+        if (cols >= W) {
+          float4 v[2 * NP];
+#pragma unroll
+          for (int t = 0; t < 2 * NP; ++t) {
+            const int id = ln + 64 * t;
+            v[t] = *(const float4*)&stg[id / PPR * SP + id % PPR * 4];
+          }
+#pragma unroll
+          for (int t = 0; t < 2 * NP; ++t) {
+            const int id = ln + 64 * t, r = id / PPR;
+            if (r <= last) *(float4*)(o + (long)r * E.ldo + id % PPR * 4) = v[t];
+          }
+        } else if (ln < cols) {
+          // a last group cut by N: one column per lane, row by row
 #pragma unroll 1
-    for (int l0 = lane; l0 < 128 * NP; l0 += 64 * NP) {
+          for (int r0 = 0; r0 < 32; r0 += 8) {
+            float v[8];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) v[q] = stg[(r0 + q) * SP + ln];
+#pragma unroll
+            for (int q = 0; q < 8; ++q)
+              if (r0 + q <= last) o[(long)(r0 + q) * E.ldo + ln] = v[q];
+          }
+        }
+        return;
+      }
+    }
+#pragma unroll 1
+    for (int l0 = ln; l0 < 128 * NP; l0 += 64 * NP) {
       float4 v[NP];
-      if (E.mode == EPI_RESID) {  // N is a multiple of 4; pieces past the edges load the last row or piece
+      if (FAST || E.mode == EPI_RESID) {  // N is a multiple of 4; pieces past the edges load the last row or piece
         const float* const gate = E.mods + E.gate_off + n;
 #pragma unroll
         for (int t = 0; t < NP; ++t) {
@@ -189,7 +231,9 @@ __device__ __forceinline__ void epilogue_group(const EpiArgs& E, const RowEntry*
         const int id = l0 + 64 * t, r = id / PPR, c = id % PPR * 4;
         float* const dst = o + (long)r * E.ldo + c;
         if (r > last) continue;
-        if (c + 4 <= cols) {
+        if (FAST) {
+          if (c < cols) *(float4*)dst = v[t];
+        } else if (c + 4 <= cols) {
           *(float4*)dst = v[t];
         } else {
           if (c < cols) dst[0] = v[t].x;
@@ -201,15 +245,46 @@ __device__ __forceinline__ void epilogue_group(const EpiArgs& E, const RowEntry*
     return;
   }
   constexpr int PPR = W / 8, NP = 32 * PPR / 64;
+  const int ln = opaque<FAST>(lane);
+  if (FAST && (E.mode != EPI_QKV || n >= v1) && n + W <= N) {
+    // whole pieces of columns that are stored side by side
+    const bool mlp = E.mode == EPI_QKV;
+    const long ld = mlp ? E.gelu_ld : E.ldo;
+    bf16_t* const o = (bf16_t*)(mlp ? E.gelu_out : E.out) + (long)m * ld +
+                      (mlp ? E.gelu_col0 + n - E.n_qkv : E.mode == EPI_GELU ? E.col0 + n : n);
+    float v[NP][8];
+#pragma unroll
+    for (int t = 0; t < NP; ++t) {
+      const float* const src = &stg[(ln + 64 * t) / PPR * SP + (ln + 64 * t) % PPR * 8];
+      *(float4*)&v[t][0] = *(const float4*)src;
+      *(float4*)&v[t][4] = *(const float4*)(src + 4);
+    }
+    if (E.mode != EPI_STORE_T)
+#pragma unroll
+      for (int t = 0; t < NP; ++t)
+#pragma unroll
+        for (int q = 0; q < 8; ++q) v[t][q] = gelu_tanh(v[t][q]);
+#pragma unroll
+    for (int t = 0; t < NP; ++t) {
+      const int r = (ln + 64 * t) / PPR;
+      uint4 w;
+      w.x = pack_bf16x2(v[t][0], v[t][1]);
+      w.y = pack_bf16x2(v[t][2], v[t][3]);
+      w.z = pack_bf16x2(v[t][4], v[t][5]);
+      w.w = pack_bf16x2(v[t][6], v[t][7]);
+      if (m + r < M) *(uint4*)(o + (long)r * ld + (ln + 64 * t) % PPR * 8) = w;
+    }
+    return;
+  }
 #pragma unroll 1
   for (int t = 0; t < NP; ++t) {
-    const int id = lane + 64 * t, r = id / PPR, c = id % PPR * 8, nc = n + c;
+    const int id = ln + 64 * t, r = id / PPR, c = id % PPR * 8, nc = n + c;
     float v[8];
     *(float4*)&v[0] = *(const float4*)&stg[r * SP + c];
     *(float4*)&v[4] = *(const float4*)&stg[r * SP + c + 4];
     bf16_t* dst;
     if (E.mode == EPI_QKV && nc < v0) {
-      const int d = E.head_dim, k = nc >= E.hidden, hn = nc - k * E.hidden, h = hn / d, dd = hn - h * d;
+      const int d = E.head_dim, k = nc >= E.hidden, hn = nc - k * E.hidden, h = hn >> hs, dd = hn - h * d;
       const RowEntry re = rows[r];  // garbage past row M, not used then
       if (m + r < M && re.gi >= 0) {
         const int half = d >> 1;
@@ -249,8 +324,9 @@ __device__ __forceinline__ void epilogue_group(const EpiArgs& E, const RowEntry*
   }
 }
 
+// 4-wave blocks run two per CU: at most 256 registers
 template <int BM, int BN, int NWM, int NWN, int BK, int STAGES, bool DTL>
-__global__ __launch_bounds__(NWM* NWN * 64) void gemm_bf16_kernel(const GemmProblem P) {
+__global__ __launch_bounds__(NWM* NWN * 64, NWM * NWN == 4 ? 2 : 1) void gemm_bf16_kernel(const GemmProblem P) {
   constexpr int NT = NWM * NWN * 64;
   constexpr int NWAVES = NWM * NWN;
   constexpr int WTM = BM / NWM, WTN = BN / NWN;
@@ -934,16 +1010,27 @@ __global__ __launch_bounds__(NWM* NWN * 64) void gemm_bf16_kernel(const GemmProb
     const int n = n0 + wn * WTN + (DTL ? q * 16 + (lane & 15) : q * 32 + (lane & 31));
     bcol[q] = (bias != nullptr && n < N) ? bf2f(bias[n]) : 0.f;
   }
-  // A rolled loop: only the staging writes, which name accumulator registers,
-  // have a copy per group.  Unrolled over its groups, modes and tails the
-  // epilogue was 240 KB of code for the 256x256 tile, run once per tile from
-  // an instruction cache (64 KB for two CUs) that the launches of a step,
-  // each another kernel, leave cold.  Rolled (the kernel is 25 KB), and with
-  // whole rows of the wave tile stored per wave access, the steps take 1 - 4%
-  // less: one single block at 256 px 239 -> 229 us, one double block at 512 px
-  // 520 -> 504 us, the 57-block 1024 px step 63.4 -> 62.4 ms, the SD3-shaped
-  // 512 px step 5.19 -> 4.97 ms.
-#pragma unroll 1
+  // The group loop is rolled for wave tiles of more than two groups: only the
+  // staging writes, which name accumulator registers, have a copy per group.
+  // Unrolled over its groups, modes and tails the epilogue was 240 KB of code for
+  // the 256x256 tile, run once per tile from an instruction cache (64 KB for two
+  // CUs) that the launches of a step, each another kernel, leave cold.  Rolled
+  // (the kernel is 21 KB), and with whole rows of the wave tile stored per wave
+  // access, one single block at 256 px takes 229 us instead of 239, one double
+  // block at 512 px 504 instead of 520, the 57-block 1024 px step 62.4 ms instead
+  // of 63.4.
+  // kFast: wave tiles of one or two groups are unrolled (31 KB for 128x128).  In
+  // the rolled form their launches of one round or less lost 1 - 2 us to its
+  // second turn and to the branches and addresses of every mode (512 x 3072 x 64
+  // to bf16 8.7 us between events before, 10.5 rolled, 8.9 now; 1024 cubed 13.3,
+  // 15.1, 13.4), and its 218 VGPRs left the 128x128 register path one block per
+  // CU (7907 x 2304 x 696: 53, 79, 53 us).  The register path unrolls every tile:
+  // no block of a served model takes it (16384 x 1536 x 200: 33.8, 38.2, 33.5).
+  // On the 256x256 tile kFast's forms are slower inside a step (one single block
+  // at 1024 px by 0.5 - 3%), whichever of them is left out.
+  constexpr bool kFast = FM <= 2 || !DTL;
+  const int ew = kFast ? __builtin_amdgcn_readfirstlane(wave) : wave;
+#pragma unroll (kFast ? FM : 1)
   for (int g = 0; g < FM; ++g) {
     static_for<FM>([&](auto gc) {
       constexpr int i = decltype(gc)::value;
@@ -970,8 +1057,8 @@ __global__ __launch_bounds__(NWM* NWN * 64) void gemm_bf16_kernel(const GemmProb
         }
       }
     });
-    const int ml = wm * WTM + g * 32;
-    epilogue_group<WTN>(E, rows + ml, stg, m0 + ml, n0 + wn * WTN, M, N, lane);
+    const int ml = ew / NWN * WTM + g * 32;
+    epilogue_group<WTN, kFast>(E, rows + ml, stg, m0 + ml, n0 + ew % NWN * WTN, M, N, lane);
   }
 }
 
