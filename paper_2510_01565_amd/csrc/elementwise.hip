@@ -6,6 +6,8 @@
 // are fixed butterfly trees (bitwise deterministic).
 #include <math.h>
 
+#include <algorithm>
+
 #include "device_common.h"
 
 namespace dit {
@@ -66,8 +68,10 @@ __device__ __forceinline__ void setup_block(const SetupArgs& a, int block, int n
 // not displace cached data); on MI355X this streams the 6.5 GB of the FLUX
 // modulation weights at about 6.8 TB/s against 5.5 TB/s for one row per wave
 // with ordinary loads.
-// The first `sblocks` blocks run the call's setup (see setup_block), which
-// nothing in this launch reads.
+// FIRST: a call's first launch, whose first `sblocks` blocks run the call's
+// setup (see setup_block, nothing in this launch reads it) and whose
+// activations may be the timestep embedding.  Both are fp64 code that needs
+// 80 VGPRs and 104 SGPRs by itself, so it stays out of the other launches.
 constexpr int GV_R = 4;
 constexpr int LN_MAX_H = 4096;  // widest hidden size (also the LayerNorm's limit)
 
@@ -78,23 +82,44 @@ struct GemvShape {
 };
 
 // MAXC: 16-byte chunks per lane and row the registers hold (K <= 64 EPC MAXC)
-template <typename WT, int MAXC>
+template <typename WT, int MAXC, bool FIRST>
 __global__ __launch_bounds__(256) void gemv_kernel(const WT* __restrict__ W, const WT* __restrict__ b,
                                                    const float* __restrict__ x, long ldx, int n_req, int K,
                                                    int N, int act, float* __restrict__ y, long ldy, TimeArgs ta,
                                                    int sblocks, const SetupArgs su) {
-  if ((int)blockIdx.x < sblocks) {
-    setup_block(su, blockIdx.x, sblocks);
-    return;
+  if constexpr (FIRST) {
+    if ((int)blockIdx.x < sblocks) {
+      setup_block(su, blockIdx.x, sblocks);
+      return;
+    }
   }
-  const int block = blockIdx.x - sblocks;
+  const int block = FIRST ? blockIdx.x - sblocks : blockIdx.x;
   using S = GemvShape<WT>;
   constexpr int EPC = S::EPC, V = S::V;
   typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
   extern __shared__ float xs[];  // [n_req][K]
   const int nr = min(n_req, GV_R);
   const int lane = threadIdx.x & 63;
-  const int nwaves = (gridDim.x - sblocks) * (blockDim.x >> 6);
+  // The activations are staged after the chunk indices are formed (fewer VGPRs,
+  // so more waves), except for the widest rows, whose two waves per SIMD gain
+  // nothing from it and whose spilled scalars grow (K 4096, four requests: 2-4%).
+  constexpr bool kStageFirst = MAXC >= 8;
+  auto stage = [&]() __attribute__((always_inline)) {
+    for (int i = threadIdx.x; i < nr * K; i += blockDim.x) {
+      const int r = i / K, k = i % K;
+      if constexpr (FIRST) {
+        if (act == GEMV_TIMESTEP) {
+          xs[i] = timestep_value(ta.t[r], k, K);
+          continue;
+        }
+      }
+      const float v = x[(long)r * ldx + k];
+      xs[i] = act == GEMV_SILU ? silu(v) : v;
+    }
+    __syncthreads();
+  };
+  if constexpr (kStageFirst) stage();
+  const int nwaves = (FIRST ? gridDim.x - sblocks : gridDim.x) * (blockDim.x >> 6);
   const int chunks = K / EPC;
   // Chunk i of a lane is chunk lane + 64 i of the row; lanes past the row's
   // last chunk load that chunk again (no branch around a load: a branch would
@@ -106,16 +131,7 @@ __global__ __launch_bounds__(256) void gemv_kernel(const WT* __restrict__ W, con
     cidx[i] = min(lane + 64 * i, chunks - 1);
     keep[i] = lane + 64 * i < chunks ? 1.f : 0.f;
   }
-  for (int i = threadIdx.x; i < nr * K; i += blockDim.x) {
-    const int r = i / K, k = i % K;
-    if (act == GEMV_TIMESTEP) {
-      xs[i] = timestep_value(ta.t[r], k, K);
-    } else {
-      const float v = x[(long)r * ldx + k];
-      xs[i] = act == GEMV_SILU ? silu(v) : v;
-    }
-  }
-  __syncthreads();
+  if constexpr (!kStageFirst) stage();
   for (int o0 = (block * (blockDim.x >> 6) + (threadIdx.x >> 6)) * V; o0 < N; o0 += nwaves * V) {
     u32x4 u[V][MAXC];
 #pragma unroll
@@ -312,13 +328,36 @@ hipError_t launch_timestep_embed(float* e, int n_req, const float* t_host, int d
 template <typename WT, int MAXC>
 void gemv_launch(int blocks, int sblocks, size_t shmem, hipStream_t s, const void* W, const void* b, const float* x,
                  long ldx, int nr, int K, int N, int act, float* y, long ldy, const TimeArgs& ta, const SetupArgs& su) {
-  hipLaunchKernelGGL((gemv_kernel<WT, MAXC>), dim3(blocks + sblocks), dim3(256), shmem, s, (const WT*)W, (const WT*)b,
-                     x, ldx, nr, K, N, act, y, ldy, ta, sblocks, su);
+  if (sblocks > 0 || act == GEMV_TIMESTEP)
+    hipLaunchKernelGGL((gemv_kernel<WT, MAXC, true>), dim3(blocks + sblocks), dim3(256), shmem, s, (const WT*)W,
+                       (const WT*)b, x, ldx, nr, K, N, act, y, ldy, ta, sblocks, su);
+  else
+    hipLaunchKernelGGL((gemv_kernel<WT, MAXC, false>), dim3(blocks), dim3(256), shmem, s, (const WT*)W, (const WT*)b, x,
+                       ldx, nr, K, N, act, y, ldy, ta, 0, su);
+}
+
+// 256-thread blocks per CU that the registers of each instance allow (its waves
+// per SIMD), by its MAXC and FIRST
+constexpr int kGemvMaxC[] = {1, 2, 3, 4, 6, 8, 16};
+constexpr int kGemvPerCuBf16[2][7] = {{8, 7, 5, 4, 3, 2, 1}, {6, 6, 5, 4, 3, 2, 1}};
+constexpr int kGemvPerCuF32[2][7] = {{8, 8, 8, 7, 4, 3, 2}, {6, 6, 6, 6, 5, 3, 2}};
+constexpr size_t kLdsPerCu = 160 * 1024;
+
+// 16-byte chunks per lane of a row of K weights
+template <typename WT>
+int gemv_chunks(int K) {
+  return (K / GemvShape<WT>::EPC + 63) / 64;
+}
+int gemv_blocks_per_cu(int wdtype, int K, bool first) {
+  const int c = wdtype == DIT_BF16 ? gemv_chunks<bf16_t>(K) : gemv_chunks<float>(K);
+  int i = 0;
+  while (kGemvMaxC[i] < c) ++i;
+  return (wdtype == DIT_BF16 ? kGemvPerCuBf16 : kGemvPerCuF32)[first][i];
 }
 
 template <typename WT, class... A>
 void gemv_dispatch(int K, A&&... a) {
-  const int c = (K / GemvShape<WT>::EPC + 63) / 64;  // chunks per lane and row
+  const int c = gemv_chunks<WT>(K);
   if (c <= 1) gemv_launch<WT, 1>(a...);
   else if (c <= 2) gemv_launch<WT, 2>(a...);
   else if (c <= 3) gemv_launch<WT, 3>(a...);
@@ -335,17 +374,23 @@ hipError_t launch_gemv(int wdtype, const void* W, const void* b, const float* x,
   const size_t shmem = (size_t)(n_req < GV_R ? n_req : GV_R) * K * sizeof(float);
   const int V = wdtype == DIT_BF16 ? GemvShape<bf16_t>::V : GemvShape<float>::V;
   int blocks = (N + 4 * V - 1) / (4 * V);
-  // Three blocks per CU are resident.  Launches of a few such rounds take one
-  // round of blocks that loop evenly instead: each new block waits for its
-  // activations before it asks for weights (36 864 rows of 3072 in bf16: 2304
-  // blocks 59 us between events, 768 blocks of 3 rounds 50).  Longer launches
-  // hide that wait (1.05 M rows: 8192 blocks 0.97 ms, 768 blocks 1.00), and
-  // below two rounds the loop would leave CUs idle (1152 blocks 20.7, 768 23.0).
-  constexpr int kResident = 3 * 256, kMaxBlocks = 256 * 32;
+  // Launches of a few rounds of resident blocks take one round of blocks that
+  // loop evenly instead: each new block waits for its activations before it asks
+  // for weights (cold weights, us between events, one block per 4 V rows against
+  // one even round; bf16, 36 864 rows: K 3072 47.0 -> 41.4 and with four requests
+  // 92 -> 69, K 4096 72 -> 56, K 2048 31.3 -> 29.6; fp32, 36 864 rows of 1024
+  // 26.7 -> 26.5, four requests 48 -> 38).  The round is what the instance's own
+  // registers and the activations' LDS hold: with three blocks per CU for every
+  // K, launches of 30 720 rows of 512 take 11.5 us instead of 9.0.  Longer
+  // launches hide that wait (262 144 rows: equal), and below two rounds the loop
+  // would leave CUs idle.
+  const int per_cu = std::min(gemv_blocks_per_cu(wdtype, K, setup || act == GEMV_TIMESTEP), (int)(kLdsPerCu / shmem));
+  const int resident = 256 * per_cu;
+  constexpr int kMaxBlocks = 256 * 32;
   if (blocks > kMaxBlocks) {
     blocks = kMaxBlocks;
-  } else if (blocks > 2 * kResident) {
-    const int rounds = (blocks + kResident - 1) / kResident;
+  } else if (blocks > 2 * resident) {
+    const int rounds = (blocks + resident - 1) / resident;
     blocks = (blocks + rounds - 1) / rounds;
   }
   SetupArgs su{};

@@ -36,3 +36,16 @@ def test_timestep_width_and_five_requests(tf):
 def test_attention_v_relayout(bf16, d, grids, n_txt):
     got, ref = _attn_case(grids, n_txt, 5, d, bf16, 22)
     assert normwise_err(got, ref) < (BF16_TOL if bf16 else F32_TOL)
+
+
+def test_modulation_rows_beyond_two_rounds_of_blocks():
+    """33 280 modulation rows of 512 in fp32: 4160 blocks against 2048 resident ones, so the GEMV's blocks loop
+    evenly; five requests, two passes.  Every block's rows reach the velocity."""
+    m = workloads.ModelShape(hidden=512, heads=8, head_dim=64, mlp_ratio=1, n_double=0, n_single=21,
+                             in_channels=16, text_dim=32, dtype="f32")
+    cfg, shapes, params = host_params(m, 23)
+    grids, n_txt, ts = [(1, 2), (2, 2), (1, 1), (1, 3), (2, 1)], [1, 0, 2, 1, 0], [0.1, 0.3, 0.5, 0.7, 0.9]
+    lat, txt = request_inputs(m, grids, n_txt, 23)
+    vel, _, _ = _run_step(m, params, shapes, cfg, grids, n_txt, ts, lat, txt)
+    ref = np.concatenate(_oracle_step(m, params, grids, n_txt, ts, lat, txt))
+    assert normwise_err(vel.cpu().numpy(), ref) < F32_TOL

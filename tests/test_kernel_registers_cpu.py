@@ -5,6 +5,7 @@ import os
 import re
 import shutil
 import subprocess
+from concurrent.futures import ThreadPoolExecutor
 
 import pytest
 
@@ -16,8 +17,6 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "--cuda-device-only", "-S
 
 def _registers(src):
     """{kernel: vector registers (VGPRs and AGPRs together)} of a source file."""
-    if not os.path.exists(HIPCC):
-        pytest.skip("hipcc not available")
     r = subprocess.run([HIPCC, *FLAGS, os.path.join(CSRC, src)], capture_output=True, text=True)
     assert r.returncode == 0, r.stderr[-2000:]
     out, name = {}, None
@@ -31,8 +30,35 @@ def _registers(src):
     return out
 
 
-def test_gemm_blocks_of_four_waves_run_two_per_cu():
-    regs = {k: v for k, v in _registers("gemm_bf16.hip").items() if "gemm_bf16_kernel" in k}
+@pytest.fixture(scope="module")
+def registers():
+    if not os.path.exists(HIPCC):
+        pytest.skip("hipcc not available")
+    srcs = ["elementwise.hip", "gemm_bf16.hip"]
+    with ThreadPoolExecutor(len(srcs)) as ex:
+        return dict(zip(srcs, ex.map(_registers, srcs)))
+
+
+def test_gemm_blocks_of_four_waves_run_two_per_cu(registers):
+    regs = {k: v for k, v in registers["gemm_bf16.hip"].items() if "gemm_bf16_kernel" in k}
     four = {k: v for k, v in regs.items() if re.search(r"ILi128ELi(64ELi4ELi1|128ELi2ELi2)E", k)}
     assert len(regs) >= 10 and len(four) == 4  # 128x64 and 128x128, direct-to-LDS and register path
     assert max(four.values()) <= 256, four
+
+
+def test_gemv_blocks_per_cu_are_the_compiled_ones(registers):
+    """launch_gemv's round of resident blocks: the table in the source against the registers of every instance
+    (blocks of four waves, so blocks per CU are waves per SIMD, eight at most)."""
+    src = open(os.path.join(CSRC, "elementwise.hip")).read()
+    maxc = [int(x) for x in re.search(r"kGemvMaxC\[\] = \{([\d, ]+)\}", src).group(1).split(",")]
+    regs = registers["elementwise.hip"]
+    for letter, name in (("t", "kGemvPerCuBf16"), ("f", "kGemvPerCuF32")):
+        table = re.search(name + r"\[2\]\[7\] = \{\{([\d, ]+)\}, \{([\d, ]+)\}\}", src)
+        for first in (0, 1):
+            want = [int(x) for x in table.group(1 + first).split(",")]
+            got = []
+            for c in maxc:
+                k = [v for n, v in regs.items() if f"gemv_kernelI{letter}Li{c}ELb{first}E" in n]
+                assert len(k) == 1, (name, c, first)
+                got.append(min(8, 512 // ((k[0] + 7) // 8 * 8)))
+            assert got == want, (name, first, got)
