@@ -633,9 +633,10 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(const AttnArgs a, const A
   constexpr float kLog2e = 1.4426950408889634f;
   __shared__ float osh[4][FQ][FD + 4];
   __shared__ float2 ml[4][FQ];  // running max (log2 domain) and sum
-  const int per_head = sc.tile_off[sc.n];
-  const int h = blockIdx.x / per_head;
-  const int t = blockIdx.x - h * per_head;
+  const int per_head = sc.tile_off[sc.n], id = block_id();
+  const int h = id / per_head;
+  const int t = id - h * per_head;
+  if (blockIdx.y > 0 && h >= a.heads) return;
   int slot = 0;
   while (slot + 1 < sc.n && t >= sc.tile_off[slot + 1]) ++slot;
   const int r = sc.req[slot];
@@ -1044,7 +1045,7 @@ hipError_t launch_attention_f32(const AttnArgs& a, hipStream_t s) {
   const AttnSched sc = make_sched(a.meta, FQ);
   const long blocks = (long)sc.tile_off[sc.n] * a.heads;
   if (blocks == 0) return hipSuccess;
-  hipLaunchKernelGGL(attn_f32_kernel, dim3((unsigned)blocks), dim3(256), 0, s, a, sc);
+  hipLaunchKernelGGL(attn_f32_kernel, grid_of(blocks), dim3(256), 0, s, a, sc);
   return hipGetLastError();
 }
 

@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <type_traits>
 #include <utility>
 
@@ -140,6 +141,16 @@ __device__ __forceinline__ void store16(T* dst, const float* v) {
     for (int q = 0; q < 4; ++q) ((float4*)dst)[q] = make_float4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
   }
 }
+
+// A launch holds fewer than 2^32 threads along x (past that the runtime wraps the
+// grid without an error): 256-thread blocks go on along y after every 2^23.
+// block_id() numbers them; where blockIdx.y > 0 it may lie past the last block,
+// which the kernel ends.
+constexpr int kGridRowLog2 = 23;
+inline dim3 grid_of(long blocks) {
+  return dim3((unsigned)std::min(blocks, 1L << kGridRowLog2), (unsigned)((blocks - 1) >> kGridRowLog2) + 1);
+}
+__device__ __forceinline__ int block_id() { return (int)(blockIdx.y << kGridRowLog2) + (int)blockIdx.x; }
 
 // XCD-aware block remap: hardware dispatches block b to XCD b % 8; return an
 // index such that every XCD owns one contiguous range of indices.

@@ -114,3 +114,31 @@ def test_vt_where_text_rows_run_into_image_rows(grids, n_txt, head_dim):
     for r, ref in enumerate(_oracle_step(m, params, grids, n_txt, ts, lat, txt)):
         assert normwise_err(got[off:off + len(ref)], ref) < BF16_TOL, r
         off += len(ref)
+
+
+def test_linear_f32_more_tiles_than_a_grid_row_holds():
+    """65 538 x 257 tiles of 32 x 32: past 2^24 blocks of 256 threads, where one grid dimension ends (the output
+    is 69 GB).  Rows and columns at both ends and at random, against fp64."""
+    import torch
+    M, N, K = 2097201, 8195, 8
+    if torch.cuda.mem_get_info()[0] < 4 * M * N + (8 << 30):
+        pytest.skip("not enough free device memory")
+    gen = torch.Generator(device="cuda").manual_seed(16)
+    x = torch.randn((M, K), generator=gen, device="cuda")
+    w = torch.randn((N, K), generator=gen, device="cuda")
+    y = torch.empty((M, N), device="cuda")
+    y.fill_(float("nan"))
+    dit.dit_linear(M, N, K, dit.DIT_F32, x, w, None, y, dit.DIT_F32)
+    torch.cuda.synchronize()
+    rng = np.random.default_rng(16)
+    rows = torch.tensor(np.unique(np.concatenate([[0, 1, 31, 32, M - 33, M - 2, M - 1], rng.integers(0, M, 500)]))).cuda()
+    ref = x[rows].double() @ w.double().T
+    # sums of 8 products of N(0, 1): rounding errors of 2^-24 of partial sums of a few units
+    assert (y[rows].double() - ref).abs().max().item() < 8 * 2 ** -24 * ref.abs().max().item()
+    cols = torch.tensor(np.unique(np.concatenate([[0, 31, 32, N - 4, N - 1], rng.integers(0, N, 60)]))).cuda()
+    for r0 in range(0, M, 1 << 18):
+        sl = slice(r0, r0 + (1 << 18))
+        err = y[sl][:, cols].double() - x[sl].double() @ w[cols].double().T
+        assert err.abs().max().item() < 1e-4, r0
+    del y
+    torch.cuda.empty_cache()
