@@ -1,5 +1,5 @@
 // Device helpers for gfx950: bf16 storage conversions, wave64 reductions,
-// activations and the per-element GEMM epilogue.
+// activations, and the numbering of blocks.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -69,77 +69,19 @@ __device__ __forceinline__ float gelu_tanh(float x) {
 
 __device__ __forceinline__ float silu(float x) { return x / (1.0f + __expf(-x)); }
 
-// One output element of a GEMM epilogue.  `y` already includes the bias;
-// `y_pair` is the value of the partner column n ^ 1 (RoPE pairs), bias included.
-template <typename T>
-__device__ __forceinline__ void epilogue_element(const EpiArgs& e, const RowEntry& row, int m, int n, float y,
-                                                 float y_pair) {
-  switch (e.mode) {
-    case EPI_STORE_F32:
-      ((float*)e.out)[(long)m * e.ldo + n] = y;
-      break;
-    case EPI_STORE_T:
-      ((T*)e.out)[(long)m * e.ldo + n] = from_f32<T>(y);
-      break;
-    case EPI_GELU:
-      ((T*)e.out)[(long)m * e.ldo + e.col0 + n] = from_f32<T>(gelu_tanh(y));
-      break;
-    case EPI_RESID: {
-      const float g = e.mods[(long)row.req * e.mods_ld + e.gate_off + n];
-      float* xo = (float*)e.out + (long)m * e.ldo + n;
-      *xo = *xo + g * y;
-      break;
-    }
-    case EPI_QKV: {
-      if (n >= e.n_qkv) {
-        ((T*)e.gelu_out)[(long)m * e.gelu_ld + e.gelu_col0 + (n - e.n_qkv)] = from_f32<T>(gelu_tanh(y));
-        break;
-      }
-      const int H = e.hidden, d = e.head_dim;
-      const int which = n / H;
-      const int hn = n - which * H;
-      const int h = hn / d, dd = hn - h * d;
-      float v = y;
-      if (which < 2 && row.gi >= 0) {
-        const int half = d >> 1;
-        const int pos = (dd < half) ? row.gi : row.gj;
-        const int kk = (dd < half ? dd : dd - half) >> 1;
-        const float2 cs = e.rope[pos * (d >> 2) + kk];
-        // even: u cos - v sin ; odd: u sin + v cos  (u = even element, v = odd element)
-        v = (dd & 1) ? (y_pair * cs.y + y * cs.x) : (y * cs.x - y_pair * cs.y);
-      }
-      if (which == 0)
-        ((T*)e.q)[((long)h * e.T + row.pos) * d + dd] = from_f32<T>(v);
-      else if (which == 1)
-        ((T*)e.k)[((long)h * e.T + row.pos) * d + dd] = from_f32<T>(v);
-      else
-        ((T*)e.vt)[((long)h * d + dd) * e.vt_ld + vt_slot(row.pos)] = from_f32<T>(v);
-      break;
-    }
-    default:
-      break;
-  }
-}
-
-// 16 consecutive values with 16-byte stores.
-template <typename T>
-__device__ __forceinline__ void store16(T* dst, const float* v) {
-  if constexpr (sizeof(T) == 2) {
-    uint4 a, b;
-    a.x = pack_bf16x2(v[0], v[1]);
-    a.y = pack_bf16x2(v[2], v[3]);
-    a.z = pack_bf16x2(v[4], v[5]);
-    a.w = pack_bf16x2(v[6], v[7]);
-    b.x = pack_bf16x2(v[8], v[9]);
-    b.y = pack_bf16x2(v[10], v[11]);
-    b.z = pack_bf16x2(v[12], v[13]);
-    b.w = pack_bf16x2(v[14], v[15]);
-    ((uint4*)dst)[0] = a;
-    ((uint4*)dst)[1] = b;
-  } else {
-#pragma unroll
-    for (int q = 0; q < 4; ++q) ((float4*)dst)[q] = make_float4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
-  }
+// 16 consecutive values as bf16, with two 16-byte stores.
+__device__ __forceinline__ void store16(bf16_t* dst, const float* v) {
+  uint4 a, b;
+  a.x = pack_bf16x2(v[0], v[1]);
+  a.y = pack_bf16x2(v[2], v[3]);
+  a.z = pack_bf16x2(v[4], v[5]);
+  a.w = pack_bf16x2(v[6], v[7]);
+  b.x = pack_bf16x2(v[8], v[9]);
+  b.y = pack_bf16x2(v[10], v[11]);
+  b.z = pack_bf16x2(v[12], v[13]);
+  b.w = pack_bf16x2(v[14], v[15]);
+  ((uint4*)dst)[0] = a;
+  ((uint4*)dst)[1] = b;
 }
 
 // A launch holds fewer than 2^32 threads along x (past that the runtime wraps the
@@ -152,13 +94,13 @@ inline dim3 grid_of(long blocks) {
 }
 __device__ __forceinline__ int block_id() { return (int)(blockIdx.y << kGridRowLog2) + (int)blockIdx.x; }
 
-// XCD-aware block remap: hardware dispatches block b to XCD b % 8; return an
-// index such that every XCD owns one contiguous range of indices.
 // Word 3 of a raw buffer resource on gfx9-family targets: 32-bit data format,
 // so untyped dword loads are range-checked against num_records and return
 // zeros past it.
 constexpr int kBufferWord3 = 0x00020000;
 
+// XCD-aware block remap: hardware dispatches block b to XCD b % 8; return an
+// index such that every XCD owns one contiguous range of indices.
 __device__ __forceinline__ int xcd_remap(int bid, int nblocks) {
   const int per = nblocks / 8, rem = nblocks % 8;
   const int xcd = bid % 8, idx = bid / 8;

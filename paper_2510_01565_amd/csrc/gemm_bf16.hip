@@ -143,7 +143,7 @@ __device__ __forceinline__ void epilogue_group(const EpiArgs& E, const RowEntry*
             float w[16];
 #pragma unroll
             for (int q = 0; q < 16; ++q) w[q] = stg[(r16 + vt_slot(q)) * SP + ln];
-            store16<bf16_t>(vt + p0 + r16, w);
+            store16(vt + p0 + r16, w);
           }
         } else {
           const int a = -p0 & 3;  // rows ahead of the first whole quad
