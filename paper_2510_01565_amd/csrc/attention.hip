@@ -925,8 +925,9 @@ size_t split_bytes(const SplitPlan& p, int head_dim) {
 //
 // At head dim 64 the softmax's vector work is the longer half of a tile, and
 // more waves per SIMD fill it: 128-query blocks run three per CU (155 VGPRs, 768
-// slots), 256-query blocks two (held to 128 VGPRs, 512 slots; one per CU at
-// 153).  wide_64() compares the two by their rounds, in units of the time a
+// slots), 256-query blocks two (held to 128 VGPRs, 512 slots; one per CU at 153;
+// 13 VGPRs are spilled, 21 in the kernel of two key groups, all of them in the
+// masked last tile, none in the loop over the tiles).  wide_64() compares the two by their rounds, in units of the time a
 // lone 128-query block takes for 1.3 times its keys, as measured at 1 792 -
 // 16 717 tokens and 3 - 24 heads: a full round costs 1.6 (768 units) and 1.95
 // (512 blocks), and the last round 0.4 / 0.87 / 1.36 for up to 1 / 2 / 3

@@ -554,9 +554,9 @@ __global__ __launch_bounds__(NWM* NWN * 64, NWM * NWN == 4 ? 2 : 1) void gemm_bf
       // cycles against 0.77 at a clock that power holds at 1.63 against 1.77
       // GHz; 4608 x 9216 x 3072: 1.29 against 1.23.  Tiles of fewer MFMAs per
       // phase (256x128, 128x256) gain 4 - 10% on repeated launches but lose
-      // 1 - 3% inside a step, where operands and code arrive cold, and keep the
-      // schedule below; raised priority for the MFMA turn and a barrier ahead
-      // of its last MFMAs measured 1% and 18% slower.
+      // 0.3 - 1.5% inside a step, where operands and code arrive cold, and keep
+      // the schedule below; raised priority for the MFMA turn and a barrier two
+      // or four MFMAs ahead of its end measured 1% and 13 - 15% slower.
       constexpr int Q = 4;
       constexpr int AF = FM2 / Q, BF = FN2, BQ = FN2 / Q;  // A fragments of a cluster; B fragments in all, and per phase
       constexpr int ASUB = A_STAGE / Q, BSUB = B_STAGE / Q;  // bytes of a part

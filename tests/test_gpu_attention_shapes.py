@@ -21,13 +21,14 @@ def _plans(profile):
     return {k.rsplit("attention_bf16_", 1)[1] for k in profile if k.startswith("detail:attention_bf16_")}
 
 
-@pytest.mark.parametrize("grids,n_txt,heads", [
-    ([(16, 24)], [0], 256),            # 768 units of 128 queries: 128-query blocks
-    ([(16, 24)], [1], 200),            # 800 units, an odd key: 400 256-query blocks of 385 keys
-    ([(23, 17)], [0], 270),            # 1080 units, 540 256-query blocks: 128-query blocks again
-    ([(16, 24), (5, 5)], [0, 3], 220), # mixed lengths: 128-query blocks
+@pytest.mark.parametrize("grids,n_txt,heads,plan", [
+    ([(16, 24)], [0], 256, "128"),            # 768 units of 128 queries
+    ([(16, 24)], [1], 200, "256"),            # 800 units, an odd key: 400 256-query blocks of 385 keys
+    ([(23, 17)], [0], 270, "128"),            # 1080 units, 540 256-query blocks: the last round nearly empty
+    ([(16, 24), (5, 5)], [0, 3], 220, "128"), # mixed lengths, more than 512 256-query blocks
+    ([(16, 24), (16, 23)], [1, 0], 120, "256"),  # mixed lengths: 840 units, 480 256-query blocks
 ])
-def test_attention_d64_dispatch(grids, n_txt, heads):
+def test_attention_d64_dispatch(grids, n_txt, heads, plan):
     import torch
     d, lens = 64, [gh * gw + nt for (gh, gw), nt in zip(grids, n_txt)]
     T = sum(lens)
@@ -36,8 +37,10 @@ def test_attention_d64_dispatch(grids, n_txt, heads):
     wsb = dit.attention_workspace_size(b, heads, d, dit.DIT_BF16)
     ws = torch.empty(wsb, dtype=torch.uint8, device="cuda")
     o = torch.full((T, heads, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+    dit.profile_start()
     dit.dit_attention(b, heads, d, dit.DIT_BF16, *(to_dev(x, torch.bfloat16) for x in (q, k, v)), o, ws, wsb)
     torch.cuda.synchronize()
+    assert _plans(dit.profile_stop()) == {plan}
     got = o.float().cpu().numpy()
     assert np.isfinite(got).all()
     hs = [0, 1, heads // 2, heads - 2, heads - 1]
